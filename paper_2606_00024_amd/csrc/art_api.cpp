@@ -106,8 +106,7 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     const int64_t n_groups = (int64_t)s->batch * s->num_kv_heads;
 
     // LDS of a workgroup: two or three chunk buffers of C*tpb tile records
-    // plus three per-loader partial aggregates each (when they fit), and
-    // three V staging buffers: half tiles (32 rows of 288 bytes) for groups
+    // and three V staging buffers: half tiles (32 rows of 288 bytes) for groups
     // of up to 4 heads, quarter tiles (4 KiB) for 8 or more.  A record of 8
     // or more heads holds 4 KiB of outputs, so when every block is one tile
     // the loaders stage V in the record the tile is about to write, and the
@@ -117,19 +116,9 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     const bool v_in_record = g >= 8 && tpb == 1;
     const size_t pbuf_bytes = v_in_record ? 0 : (g >= 8 ? (size_t)3 * 4096 : (size_t)3 * 32 * 288) + 16;
     const size_t lds_cap = 78 * 1024;
-    auto lds_for = [&](int blocks, int partials, int slots = 2) {
-        return slots * (size_t)(blocks + partials) * rec_bytes + pbuf_bytes;
-    };
-    // the per-loader partials save the resolver a fold over the blocks; they
-    // are kept unless dropping them lets a chunk hold more blocks (up to 8)
-    auto blocks_fitting = [&](int partials) {
-        int b = art::kMaxChunkBlocks;
-        while (b > 0 && lds_for(b, partials) > lds_cap) --b;
-        return b;
-    };
-    const int b3 = blocks_fitting(3), b0 = blocks_fitting(0);
-    const int partials = (b3 >= 1 && b3 >= (b0 < 8 ? b0 : 8)) ? 3 : 0;
-    int c_max = partials ? b3 : b0;
+    auto lds_for = [&](int blocks, int slots) { return slots * (size_t)blocks * rec_bytes + pbuf_bytes; };
+    int c_max = art::kMaxChunkBlocks;
+    while (c_max > 0 && lds_for(c_max, 2) > lds_cap) --c_max;
     // a loader streams at most kMaxChunkTiles tiles of a chunk
     while (c_max > 1 && (c_max + 2) / 3 * tpb > art::kMaxChunkTiles) --c_max;
     if (c_max < 1) return ART_ERR_UNSUPPORTED;
@@ -172,12 +161,11 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     p->n_groups = (int32_t)n_groups;
     p->t_cap = (int32_t)t_cap;
     p->record_floats = (g * art::kHeadDim + 2 * g + 63) / 64 * 64;
-    p->loader_partials = partials;
     p->v_in_record = v_in_record ? 1 : 0;
     // (a third buffer was measured: it lets loaders run further past a
     // stop and gains nothing elsewhere)
     p->slots = 2;
-    p->lds_bytes = lds_for(C, partials, p->slots);
+    p->lds_bytes = lds_for(C, p->slots);
 
     art::WorkspaceLayout& w = p->ws;
     size_t off = 0;
@@ -238,6 +226,8 @@ art_status enqueue_decode(const Plan& plan, const art_decode_shape* shape,
     k.vs_page = shape->v_stride_page;
     k.vs_head = shape->v_stride_head;
     k.vs_tok = shape->v_stride_token;
+    // the narrow form's lane offsets are products of 24-bit factors
+    k.wide = 2 * k.ks_tok >= (1 << 24) || 2 * k.vs_tok >= (1 << 24);
     k.scale_log2 = (float)((double)opts->softmax_scale * 1.4426950408889634);
     k.tau = opts->tau;
     k.phi = opts->phi;
@@ -266,7 +256,6 @@ art_status enqueue_decode(const Plan& plan, const art_decode_shape* shape,
     }
     k.record_floats = plan.record_floats;
     k.chunk_recs_lds = plan.chunk_blocks;
-    k.loader_partials = plan.loader_partials;
     k.v_in_record = plan.v_in_record;
     k.q = static_cast<const uint16_t*>(q);
     k.k = static_cast<const uint16_t*>(k_cache);

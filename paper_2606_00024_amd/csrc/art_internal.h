@@ -56,7 +56,6 @@ struct Plan {
     int32_t n_groups;        // batch * num_kv_heads
     int32_t t_cap;           // traversal length bound per group
     int32_t record_floats;   // floats per aggregate / inclusive record
-    int32_t loader_partials; // see KernelParams
     int32_t v_in_record;     // see KernelParams
     int32_t slots;           // chunk buffers in LDS (2 or 3)
     size_t lds_bytes;        // dynamic LDS per workgroup
@@ -82,9 +81,9 @@ struct KernelParams {
     int32_t lead_chunks, lead_blocks;  // the first lead_chunks chunks hold lead_blocks blocks
     int32_t work_chunks;     // chunk rows of the work list (<= max_chunks)
     int32_t chunk_recs_lds;  // block records per LDS chunk buffer
-    int32_t loader_partials; // per-loader partial aggregates kept in LDS (3 or 0)
     int32_t n_slots;         // chunk buffers in LDS (2 or 3)
     int32_t v_in_record;     // 1: V is staged in the LDS record being written (no staging buffers)
+    int32_t wide;            // 1: rows of K or of V lie 8 MiB or more apart (64-bit lane addresses)
     int32_t look_first;      // 1: a chunk looks back once before publishing its aggregate (set at launch)
     // data
     const uint16_t* q;

@@ -31,16 +31,16 @@
 //   once a stop before it is announced.
 //
 //   Resolver (wavefront 0), per ready chunk:
-//     - folds the loaders' partials into the chunk aggregate;
+//     - folds the blocks' records into the chunk aggregate;
 //     - obtains the softmax state after the previous chunk (that chunk's
 //       inclusive state, or the nearest inclusive state found by looking
 //       back with the aggregates after it folded forward: always the same
 //       left fold, so results never depend on timing) and publishes its own
 //       inclusive state at once;
-//     - replays its blocks from that prefix, running the stability test per
-//       block (normalised running output o(t), increment d = o(t) - o(t-1),
-//       d_scale = |d|, d_direction = 1 - cos from |o|^2, |d|^2 and o.d
-//       without cancellation);
+//     - replays its blocks from that prefix (normalised running output o(t),
+//       increment d = o(t) - o(t-1)) and then runs the stability test on all
+//       of them at once (d_scale = |d|, d_direction = 1 - cos from |o|^2,
+//       |d|^2 and o.d without cancellation);
 //     - publishes a stability summary, and announces "stop at or before this
 //       chunk" at once when the chunk's own blocks hold a run of p stable
 //       steps; if the chunk can hold the stop (or is the group's last chunk)
@@ -69,6 +69,13 @@ constexpr int kD = kHeadDim;
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
 __device__ __forceinline__ float bf_hi(uint32_t w) { return __uint_as_float(w & 0xffff0000u); }
 
+// two floats to two bf16 (round to nearest even), one v_cvt_pk_bf16_f32
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+
 __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
   uint32_t u = __float_as_uint(f);
   if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;  // NaN
@@ -85,6 +92,13 @@ constexpr int kQuadXor1 = 0xB1;       // quad_perm [1,0,3,2]
 constexpr int kQuadXor2 = 0x4E;       // quad_perm [2,3,0,1]
 constexpr int kRowHalfMirror = 0x141; // lane i <- lane 7-i within each 8
 constexpr int kRowMirror = 0x140;     // lane i <- lane 15-i within each 16
+constexpr int kRowRor4 = 0x124;       // lane i <- lane i-4 of its row of 16 (= i+12)
+constexpr int kRowRor8 = 0x128;       // lane i <- lane i-8 (= i+8)
+constexpr int kRowRor12 = 0x12C;      // lane i <- lane i-12 (= i+4)
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp_u(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
+}
 
 // Every lane of the row ends with the same bits (each step adds the same two
 // partial sums, only in swapped operand order).
@@ -101,6 +115,35 @@ __device__ __forceinline__ float row_max(float x) {
   x = fmaxf(x, dpp_f<kRowHalfMirror>(x));
   x = fmaxf(x, dpp_f<kRowMirror>(x));
   return x;
+}
+
+__device__ __forceinline__ float read_lane(float x, int lane) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(x), lane));
+}
+// Maximum and sum over the four rows of 16 lanes (lanes l, l ^ 16, l ^ 32,
+// l ^ 48), by gfx950's half swaps: each swap hands every lane both operands
+// in the same order, so all four lanes end with the same bits.
+__device__ __forceinline__ void swap_rows16(float x, float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_int(x), __float_as_int(x), false, false);
+  a = __int_as_float(r[0]);
+  b = __int_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_rows32(float x, float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_int(x), __float_as_int(x), false, false);
+  a = __int_as_float(r[0]);
+  b = __int_as_float(r[1]);
+}
+__device__ __forceinline__ float rows_max(float x) {
+  float a, b;
+  swap_rows16(x, a, b);
+  swap_rows32(fmaxf(a, b), a, b);
+  return fmaxf(a, b);
+}
+__device__ __forceinline__ float rows_sum(float x) {
+  float a, b;
+  swap_rows16(x, a, b);
+  swap_rows32(a + b, a, b);
+  return a + b;
 }
 
 // LDS written by some lanes of this wave, read by others.  LDS operations of
@@ -228,6 +271,8 @@ struct Cfg {
   static constexpr int HPL = G >= 4 ? G / 4 : 1;   // head slots per lane (state layout)
   static constexpr int HC = G > 8 ? 8 : G;          // heads per P.V pass
   static constexpr int REC = G * kD + 2 * G;        // floats per LDS tile record
+  static constexpr int REP = G > 8 ? 1 : G > 4 ? 2 : 4;  // copies of the heads over the 16 score columns
+  static constexpr int COLS = 16 / REP;             // columns of one copy
 };
 
 // Per-head softmax state in the "state layout": lane l covers dims
@@ -257,13 +302,72 @@ __device__ __forceinline__ bool slot_valid(int lane, int k) {
   return ((lane >> 4) + 4 * k) < G;
 }
 
-// s <- s (+) p : softmax-weighted merge of two disjoint token sets.
-// o_new = o + w (o_p - o) with w = mass_p / (mass_s + mass_p) (the increment
-// form of Appendix A).  Written with explicit operations so that every call
-// site produces the same bits.  Optionally returns the increment d.
-template <int G, bool WANT_DELTA>
-__device__ __forceinline__ void merge(State<G>& s, const State<G>& p,
-                                      float (*delta)[8] = nullptr) {
+// s <- s (+) p_0 (+) p_1 ... : softmax-weighted merges of disjoint token
+// sets, left to right (the increment form of Appendix A, per head)
+//   m' = max(m, m_i), L' = L 2^(m - m') + L_i 2^(m_i - m'),
+//   o' = o + w (o_i - o), w = L_i 2^(m_i - m') / L'.
+// A run of up to 16 records is merged in two parts.  First, once, lane
+// (r, c) takes record c of head r + 4k: the running maxima come from a
+// prefix maximum over the 16 lanes of a row (exact), and with them every
+// record's factors old = 2^(m - m') and add = L_i 2^(m_i - m'), all records
+// at once.  Then step by step: two operations for L', one reciprocal, three
+// operations per output.  The results are those of merging one record after
+// the other, bit for bit, wherever a run is cut.  (Each record's exponentials
+// and their latency inside the step took the resolver 0.55 us a block.)
+template <int G>
+struct Run {
+  float m[Cfg<G>::HPL];    // lane (r, c): maximum after record c
+  float old[Cfg<G>::HPL];  // factor of the mass before record c
+  float add[Cfg<G>::HPL];  // mass that record c adds
+};
+
+template <int CTRL>
+__device__ __forceinline__ float dpp_old(float old, float x) {
+  return __int_as_float(__builtin_amdgcn_update_dpp(__float_as_int(old), __float_as_int(x), CTRL, 0xf, 0xf, false));
+}
+constexpr int kRowShr1 = 0x111, kRowShr2 = 0x112, kRowShr4 = 0x114, kRowShr8 = 0x118;
+
+// m0: the state's maximum (-inf when it is empty), m, L: this lane's record
+// (L = 0 past the run's end)
+template <int G>
+__device__ __forceinline__ void run_factors(Run<G>& f, int k, float m0, float m, float L) {
+  const bool v = L > 0.f;
+  float x = v ? m : kNegInf;
+  x = fmaxf(x, dpp_old<kRowShr1>(kNegInf, x));
+  x = fmaxf(x, dpp_old<kRowShr2>(kNegInf, x));
+  x = fmaxf(x, dpp_old<kRowShr4>(kNegInf, x));
+  x = fmaxf(x, dpp_old<kRowShr8>(kNegInf, x));
+  x = fmaxf(x, m0);
+  const float before = dpp_old<kRowShr1>(m0, x);
+  f.m[k] = x;
+  f.old[k] = before == kNegInf ? 0.f : fast_exp2(__fsub_rn(before, x));
+  f.add[k] = v ? __fmul_rn(L, fast_exp2(__fsub_rn(m, x))) : 0.f;
+}
+
+// the value of lane i of this lane's row
+__device__ __forceinline__ float row_lane(float x, int i, int lane) {
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * ((lane & 48) | i), __float_as_int(x)));
+}
+
+// One step: record i of the run into slot k of the state; `p` is the
+// record's output.  d receives the increment.
+template <int G>
+__device__ __forceinline__ void run_step(State<G>& s, const Run<G>& f, int k, int i, int lane, const float (&p)[8],
+                                         float (&d)[8]) {
+  const float old = row_lane(f.old[k], i, lane), add = row_lane(f.add[k], i, lane);
+  const float Ln = __fadd_rn(__fmul_rn(s.L[k], old), add);
+  const float w = add > 0.f ? (s.L[k] > 0.f ? __fmul_rn(add, fast_rcp(Ln)) : 1.f) : 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    d[e] = __fmul_rn(w, __fsub_rn(p[e], s.o[k][e]));
+    s.o[k][e] = __fadd_rn(s.o[k][e], d[e]);
+  }
+  s.L[k] = Ln;
+}
+
+// One whole record (in state layout) into the state.
+template <int G>
+__device__ __forceinline__ void merge(State<G>& s, const State<G>& p) {
 #pragma unroll
   for (int k = 0; k < Cfg<G>::HPL; ++k) {
     const bool v1 = s.L[k] > 0.f;
@@ -274,49 +378,68 @@ __device__ __forceinline__ void merge(State<G>& s, const State<G>& p,
     const float Ln = __fadd_rn(a, bb);
     const float w = v2 ? (v1 ? __fmul_rn(bb, fast_rcp(Ln)) : 1.f) : 0.f;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float d = __fmul_rn(w, __fsub_rn(p.o[k][e], s.o[k][e]));
-      if (WANT_DELTA) delta[k][e] = d;
-      s.o[k][e] = __fadd_rn(s.o[k][e], d);
-    }
+    for (int e = 0; e < 8; ++e)
+      s.o[k][e] = __fadd_rn(s.o[k][e], __fmul_rn(w, __fsub_rn(p.o[k][e], s.o[k][e])));
     s.m[k] = (v1 || v2) ? mn : kNegInf;
     s.L[k] = Ln;
   }
 }
 
 // ---- records: workspace (coherent, normalised) and LDS tiles --------------
-// Record layout: o[G][128] | m[G] | L[G].
+// LDS block record: o[G][128] | m[G] | L[G], the block's normalised output
+// (the loaders normalise it when they write it), its maximum and its mass.
 template <int G>
-__device__ __forceinline__ void write_state(float* rec, const State<G>& s, int lane) {
-  const int c = lane & 15, r = lane >> 4;
-#pragma unroll
-  for (int k = 0; k < Cfg<G>::HPL; ++k) {
-    const int h = r + 4 * k;
-    if (h < G) {
-      f32x4* dst = reinterpret_cast<f32x4*>(rec + h * kD + c * 8);
-      dst[0] = f32x4{s.o[k][0], s.o[k][1], s.o[k][2], s.o[k][3]};
-      dst[1] = f32x4{s.o[k][4], s.o[k][5], s.o[k][6], s.o[k][7]};
-      if (c == 0) {
-        rec[G * kD + h] = s.m[k];
-        rec[G * kD + G + h] = s.L[k];
-      }
-    }
-  }
+__device__ __forceinline__ void read_output(const float* rec, int k, int lane, float (&o)[8]) {
+  const int c = lane & 15;
+  int h = (lane >> 4) + 4 * k;
+  if (h >= G) h = 0;  // idle slot: read something valid, never used
+  const f32x4* src = reinterpret_cast<const f32x4*>(rec + h * kD + c * 8);
+  const f32x4 x0 = src[0], x1 = src[1];
+  o[0] = x0[0]; o[1] = x0[1]; o[2] = x0[2]; o[3] = x0[3];
+  o[4] = x1[0]; o[5] = x1[1]; o[6] = x1[2]; o[7] = x1[3];
+}
+// Lane (r, c): maximum and mass of block c for head r + 4k (an empty record
+// from block nb on).
+template <int G>
+__device__ __forceinline__ void read_masses(const float* blocks, int nb, int k, int lane, float& m, float& L) {
+  const int c = lane & 15;
+  int h = (lane >> 4) + 4 * k;
+  if (h >= G) h = 0;
+  const float* rec = blocks + min(c, nb - 1) * Cfg<G>::REC + G * kD + h;
+  m = rec[0];
+  L = c < nb ? rec[G] : 0.f;
 }
 
+// The chunk's aggregate: the state of its blocks alone.  The weights of all
+// blocks come at once (lane (r, c): block c), then one fused multiply-add
+// per block and output.
 template <int G>
-__device__ __forceinline__ void read_state(const float* rec, State<G>& s, int lane) {
-  const int c = lane & 15, r = lane >> 4;
+__device__ __forceinline__ void aggregate(State<G>& s, const float* blocks, int nb, int lane) {
+  constexpr int HPL = Cfg<G>::HPL;
+  float w[HPL];
 #pragma unroll
-  for (int k = 0; k < Cfg<G>::HPL; ++k) {
-    int h = r + 4 * k;
-    if (h >= G) h = 0;  // idle slot: read something valid, never used
-    const f32x4* src = reinterpret_cast<const f32x4*>(rec + h * kD + c * 8);
-    const f32x4 x0 = src[0], x1 = src[1];
-    s.o[k][0] = x0[0]; s.o[k][1] = x0[1]; s.o[k][2] = x0[2]; s.o[k][3] = x0[3];
-    s.o[k][4] = x1[0]; s.o[k][5] = x1[1]; s.o[k][6] = x1[2]; s.o[k][7] = x1[3];
-    s.m[k] = rec[G * kD + h];
-    s.L[k] = rec[G * kD + G + h];
+  for (int k = 0; k < HPL; ++k) {
+    float m, L;
+    read_masses<G>(blocks, nb, k, lane, m, L);
+    const bool v = L > 0.f;
+    const float top = row_max(v ? m : kNegInf);
+    const float x = v ? __fmul_rn(L, fast_exp2(__fsub_rn(m, top))) : 0.f;
+    s.m[k] = top;
+    s.L[k] = row_sum(x);
+    w[k] = s.L[k] > 0.f ? __fmul_rn(x, fast_rcp(s.L[k])) : 0.f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) s.o[k][e] = 0.f;
+  }
+#pragma unroll 2
+  for (int i = 0; i < nb; ++i) {
+#pragma unroll
+    for (int k = 0; k < HPL; ++k) {
+      float p[8];
+      read_output<G>(blocks + i * Cfg<G>::REC, k, lane, p);
+      const float wi = row_lane(w[k], i, lane);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s.o[k][e] = __builtin_fmaf(wi, p[e], s.o[k][e]);
+    }
   }
 }
 
@@ -358,34 +481,36 @@ __device__ __forceinline__ void publish_state(__amdgpu_buffer_rsrc_t rs, int rec
   }
 }
 
+__device__ __forceinline__ float ld_record(__amdgpu_buffer_rsrc_t rs, int off) {
+  return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, off * 4, 0, kCoherent));
+}
+template <int G>
+__device__ __forceinline__ void fetch_output(__amdgpu_buffer_rsrc_t rs, int rec_off, int k, int lane, float (&o)[8]) {
+  const int c = lane & 15;
+  int h = (lane >> 4) + 4 * k;
+  if (h >= G) h = 0;
+  const int off = (rec_off + h * kD + c * 4) * 4;
+  const f32x4 x0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kCoherent);
+  const f32x4 x1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 256, 0, kCoherent);
+  o[0] = x0[0]; o[1] = x0[1]; o[2] = x0[2]; o[3] = x0[3];
+  o[4] = x1[0]; o[5] = x1[1]; o[6] = x1[2]; o[7] = x1[3];
+}
 template <int G>
 __device__ __forceinline__ void fetch_state(__amdgpu_buffer_rsrc_t rs, int rec_off, State<G>& s, int lane) {
-  const int c = lane & 15, r = lane >> 4;
 #pragma unroll
   for (int k = 0; k < Cfg<G>::HPL; ++k) {
-    int h = r + 4 * k;
+    int h = (lane >> 4) + 4 * k;
     if (h >= G) h = 0;
-    const int off = (rec_off + h * kD + c * 4) * 4;
-    const f32x4 x0 = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, kCoherent);
-    const f32x4 x1 = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 256, 0, kCoherent);
-    s.o[k][0] = x0[0]; s.o[k][1] = x0[1]; s.o[k][2] = x0[2]; s.o[k][3] = x0[3];
-    s.o[k][4] = x1[0]; s.o[k][5] = x1[1]; s.o[k][6] = x1[2]; s.o[k][7] = x1[3];
-    s.m[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (rec_off + G * kD + h) * 4, 0, kCoherent));
-    s.L[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, (rec_off + G * kD + G + h) * 4, 0, kCoherent));
+    s.m[k] = ld_record(rs, rec_off + G * kD + h);
+    s.L[k] = ld_record(rs, rec_off + G * kD + G + h);
+    fetch_output<G>(rs, rec_off, k, lane, s.o[k]);
   }
-}
-
-// An LDS block record holds the block's normalised output (the loaders
-// normalise it when they write it), its running max and its mass.
-template <int G>
-__device__ __forceinline__ void read_tile(const float* rec, State<G>& s, int lane) {
-  read_state<G>(rec, s, lane);
 }
 
 // ---- phase 1: one 64-token tile on one wavefront ---------------------------
 template <int G>
 __device__ __forceinline__ void load_q(const KernelParams& P, int b, int kvh, int lane, bf16x8 (&qa)[4]) {
-  const int h = lane & 15;
+  const int h = lane & (Cfg<G>::COLS - 1);
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
     if (h < G) {
@@ -437,7 +562,7 @@ __device__ __forceinline__ int vstage_off(int row, int piece) {
 // The first tile of a block writes the block record; each later tile of
 // the block (accumulate) is folded into it: both parts rescaled to the
 // larger running max and the combined mass, in tile order.
-template <int G>
+template <int G, bool WIDE>
 __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, const int (&pg)[4],
                              const bf16x8 (&qa)[4], uint16_t* __restrict__ vbuf,
                              float* __restrict__ rec, bool accumulate) {
@@ -459,22 +584,45 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
   // A 16-aligned group never straddles a page (page_size >= 16, power of
   // two); tokens past L are redirected to token L-1, which lies in the same
   // group or in the last group before it, the group whose page pg[n] then
-  // names.
+  // names.  V: lane (lo, g) holds token 4i + g, dims 8lo .. +7; the four
+  // tokens of one load instruction are consecutive and lie in group i / 4.
+  // All are issued together so that one memory latency covers the tile.
+  // Rows up to 8 MiB apart (WIDE false, every usual layout) are addressed
+  // from scalar group bases with 24-bit lane products: the general form's
+  // 64-bit multiplies per lane (36 of them) kept a tile's first loads waiting.
   u32x4 kr[4][4];
-#pragma unroll
-  for (int n = 0; n < 4; ++n) {
-    const int tok = min(tok0 + 16 * n + lo, L - 1);
-    const uint16_t* kp = P.k + (int64_t)pg[n] * P.ks_page + (int64_t)kvh * P.ks_head +
-                         (int64_t)(tok & psz_mask) * P.ks_tok;
-#pragma unroll
-    for (int s = 0; s < 4; ++s)
-      kr[n][s] = *reinterpret_cast<const u32x4*>(kp + (4 * s + g) * 8);
-  }
-  // V: lane (lo, g) holds token 4i + g, dims 8lo .. +7; the four tokens of
-  // one load instruction are consecutive and lie in group i / 4.  Issued
-  // with the K loads so that one memory latency covers the whole tile.
   u32x4 vr[16];
-  {
+  if constexpr (!WIDE) {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int t = min(tok0 + 16 * n, L - 1);
+      const char* kb = reinterpret_cast<const char*>(P.k + (int64_t)pg[n] * P.ks_page + (int64_t)kvh * P.ks_head +
+                                                     (int64_t)(t & psz_mask) * P.ks_tok);
+      const uint32_t ko = __umul24(min(lo, L - 1 - t), (uint32_t)(2 * P.ks_tok)) + 16u * g;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) kr[n][s] = *reinterpret_cast<const u32x4*>(kb + (ko + 64u * s));
+    }
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int t = min(tok0 + 16 * n, L - 1);
+      const char* vb = reinterpret_cast<const char*>(P.v + (int64_t)pg[n] * P.vs_page + (int64_t)kvh * P.vs_head +
+                                                     (int64_t)(t & psz_mask) * P.vs_tok);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t vo = __umul24(min(4 * j + g, L - 1 - t), (uint32_t)(2 * P.vs_tok)) + 16u * lo;
+        vr[4 * n + j] = *reinterpret_cast<const u32x4*>(vb + vo);
+      }
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < 4; ++n) {
+      const int tok = min(tok0 + 16 * n + lo, L - 1);
+      const uint16_t* kp = P.k + (int64_t)pg[n] * P.ks_page + (int64_t)kvh * P.ks_head +
+                           (int64_t)(tok & psz_mask) * P.ks_tok;
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        kr[n][s] = *reinterpret_cast<const u32x4*>(kp + (4 * s + g) * 8);
+    }
     const uint16_t* vp = P.v + (int64_t)kvh * P.vs_head + lo * 8;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
@@ -485,7 +633,14 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
   }
   __builtin_amdgcn_sched_barrier(0);
 
-  // S^T[n][r]: token 16n + 4g + r, head lo.
+  // S^T[n][r]: token 16n + 4g + r, head lo mod COLS: the 16 columns hold REP
+  // copies of the heads, and copy u = lo / COLS keeps the scores of the
+  // groups n = REP i + u.  Each lane's softmax work is then NS x 4 tokens in
+  // place of 16 with most lanes idle (at g = 4: 4), which with the packed
+  // conversions below took a tile's vector ALU instructions from about 650
+  // to 200.
+  constexpr int REP = Cfg<G>::REP, COLS = Cfg<G>::COLS, NS = 4 / REP;
+  const int u = lo / COLS;
   f32x4 St[4];
 #pragma unroll
   for (int n = 0; n < 4; ++n) {
@@ -494,64 +649,94 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
     for (int s = 0; s < 4; ++s)
       St[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, kr[n][s]), qa[s], St[n], 0, 0, 0);
   }
-  // softmax of head lo over the tile: the lane's 16 tokens, then the four
-  // lanes lo, lo+16, lo+32, lo+48 (every lane of a column ends with the
-  // same bits: max is exact and each step adds the same two values)
-  float sc[4][4];
+  // softmax of the lane's head over the tile: the lane's own tokens, the
+  // other copies (lanes lo ^ 8, then lo +- 4 of the row), then the four rows
+  // (every lane of a head ends with the same bits: max is exact and each
+  // step adds the same two values)
+  float sc[NS][4];
   float mx = kNegInf;
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+  for (int i = 0; i < NS; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool ok = (lo < G) && (tok0 + 16 * n + 4 * g + r < L);
-      sc[n][r] = ok ? St[n][r] * P.scale_log2 : kNegInf;
-      mx = fmaxf(mx, sc[n][r]);
+      float x = St[REP * i][r];
+      if constexpr (REP == 2) {
+        x = u ? St[2 * i + 1][r] : x;
+      } else if constexpr (REP == 4) {
+        const float y = (u & 1) ? St[1][r] : x, z = (u & 1) ? St[3][r] : St[2][r];
+        x = (u & 2) ? z : y;
+      }
+      sc[i][r] = x * P.scale_log2;
     }
-  mx = fmaxf(mx, __shfl_xor(mx, 16));
-  mx = fmaxf(mx, __shfl_xor(mx, 32));
+  if (tok0 + kTile > L) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (tok0 + 16 * (REP * i + u) + 4 * g + r >= L) sc[i][r] = kNegInf;
+  }
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) mx = fmaxf(mx, sc[i][r]);
+  if constexpr (REP >= 2) mx = fmaxf(mx, dpp_f<kRowRor8>(mx));
+  if constexpr (REP == 4) mx = fmaxf(mx, dpp_f<kRowRor4>(mx));
+  mx = rows_max(mx);
   float ls = 0.f;
 #pragma unroll
-  for (int n = 0; n < 4; ++n)
+  for (int i = 0; i < NS; ++i)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const float p = mx == kNegInf ? 0.f : fast_exp2(sc[n][r] - mx);
-      sc[n][r] = p;
+      const float p = mx == kNegInf ? 0.f : fast_exp2(sc[i][r] - mx);
+      sc[i][r] = p;
       ls += p;
     }
-  ls = ls + __shfl_xor(ls, 16);
-  ls = ls + __shfl_xor(ls, 32);
+  if constexpr (REP >= 2) ls = ls + dpp_f<kRowRor8>(ls);
+  if constexpr (REP == 4) ls = ls + dpp_f<kRowRor4>(ls);
+  ls = rows_sum(ls);
   if (g == 0 && lo < G && !accumulate) {
     rec[G * kD + lo] = mx;
     rec[G * kD + G + lo] = ls;
   }
 
   // A operands of the two 32-token K-steps c: element e of lane (lo, g) is
-  // p of head lo at token 16(2c + e/4) + 4g + e%4, in three bf16 parts.
+  // p of head lo at token 16(2c + e/4) + 4g + e%4, in three bf16 parts (hi +
+  // mid + lo carries 24 significant bits).  The groups that other copies
+  // hold come from lanes lo + COLS, lo + 2 COLS, ... of the row; the rows of
+  // A past the last head then hold other lanes' values, which only reach
+  // accumulator rows that nothing reads.
+  uint32_t own[NS][3][2];
+#pragma unroll
+  for (int i = 0; i < NS; ++i)
+#pragma unroll
+    for (int e = 0; e < 2; ++e) {
+      float a0 = sc[i][2 * e], a1 = sc[i][2 * e + 1];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const uint32_t w = pack_bf16(a0, a1);
+        own[i][j][e] = w;
+        a0 = a0 - bf_lo(w);
+        a1 = a1 - bf_hi(w);
+      }
+    }
   bf16x8 a[2][3];
 #pragma unroll
-  for (int c = 0; c < 2; ++c) {
-    uint32_t w[3][4];
+  for (int j = 0; j < 3; ++j)
 #pragma unroll
-    for (int e2 = 0; e2 < 4; ++e2) {
-      uint32_t part[3][2];
-#pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int e = 2 * e2 + h;
-        const float p = sc[2 * c + (e >> 2)][e & 3];
-        const uint32_t b0 = f32_to_bf16_bits(p);
-        const float r1 = p - __uint_as_float(b0 << 16);
-        const uint32_t b1 = f32_to_bf16_bits(r1);
-        const float r2 = r1 - __uint_as_float(b1 << 16);
-        part[0][h] = b0;
-        part[1][h] = b1;
-        part[2][h] = f32_to_bf16_bits(r2);
+    for (int c = 0; c < 2; ++c) {
+      u32x4 w;
+      if constexpr (REP == 1) {
+        w = u32x4{own[2 * c][j][0], own[2 * c][j][1], own[2 * c + 1][j][0], own[2 * c + 1][j][1]};
+      } else if constexpr (REP == 2) {
+        w = u32x4{own[c][j][0], own[c][j][1], dpp_u<kRowRor8>(own[c][j][0]), dpp_u<kRowRor8>(own[c][j][1])};
+      } else if (c == 0) {
+        w = u32x4{own[0][j][0], own[0][j][1], dpp_u<kRowRor12>(own[0][j][0]), dpp_u<kRowRor12>(own[0][j][1])};
+      } else {
+        w = u32x4{dpp_u<kRowRor8>(own[0][j][0]), dpp_u<kRowRor8>(own[0][j][1]),
+                  dpp_u<kRowRor4>(own[0][j][0]), dpp_u<kRowRor4>(own[0][j][1])};
       }
-#pragma unroll
-      for (int j = 0; j < 3; ++j) w[j][e2] = part[j][0] | (part[j][1] << 16);
+      a[c][j] = __builtin_bit_cast(bf16x8, w);
     }
-#pragma unroll
-    for (int j = 0; j < 3; ++j) a[c][j] = __builtin_bit_cast(bf16x8, u32x4{w[j][0], w[j][1], w[j][2], w[j][3]});
-  }
 
   // P.V over the two halves of the tile.  B for K-step c and dims
   // 16d .. 16d+15: lane (lo, g) needs V[token of element e][16d + lo]; in
@@ -618,12 +803,15 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
   // staging buffer, which the P.V loop no longer reads (a record never
   // stages its own later tiles: records stage only blocks of one tile).
   if (!accumulate) {
+    // 1 / l_h of lane h, handed to the lanes that hold head h's sums
+    const float inv_l = ls > 0.f ? fast_rcp(ls) : 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       const int h = 4 * g + r;
       if (h < G) {
-        const float l = rec[G * kD + G + h];
-        const float inv = l > 0.f ? fast_rcp(l) : 0.f;
+        float inv = read_lane(inv_l, r);
+        if constexpr (G > 4) inv = g == 1 ? read_lane(inv_l, 4 + r) : inv;
+        if constexpr (G > 8) inv = g == 2 ? read_lane(inv_l, 8 + r) : g == 3 ? read_lane(inv_l, 12 + r) : inv;
 #pragma unroll
         for (int d = 0; d < 8; ++d) rec[h * kD + 16 * d + lo] = __fmul_rn(acc[d][r], inv);
       }
@@ -659,6 +847,18 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
     }
   }
   wave_lds_sync();  // the scale factors are read before the buffer is reused
+}
+
+// One block of the chunk into the state (the replay's step).
+template <int G>
+__device__ __forceinline__ void step_block(State<G>& s, const Run<G>& run, const float* blocks, int i, int lane) {
+#pragma unroll
+  for (int k = 0; k < Cfg<G>::HPL; ++k) {
+    float p[8], d[8];
+    read_output<G>(blocks + i * Cfg<G>::REC, k, lane, p);
+    run_step<G>(s, run, k, i, lane, p, d);
+    s.m[k] = row_lane(run.m[k], i, lane);
+  }
 }
 
 // ---- phase 2 helpers ----------------------------------------------------------
@@ -992,6 +1192,8 @@ constexpr int kMetaLen = 6, kMetaListLen = 7;  // raw seq_len and list length of
 __device__ __forceinline__ int lds_ld(const int* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
+// the same word for every lane of the wave, in a scalar register
+__device__ __forceinline__ int lds_uniform(const int* p) { return __builtin_amdgcn_readfirstlane(lds_ld(p)); }
 __device__ __forceinline__ void lds_st(int* p, int v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
@@ -1094,8 +1296,8 @@ __device__ int stab_scan(const KernelParams& P, int gidx, int me, int lane) {
 
 template <int G>
 __device__ void resolve_heads(const KernelParams& P, int gidx, int k, const GroupInfo& gi,
-                              const float* blocks, const State<G>& pre, uint32_t head_bits,
-                              int t0, int nb, int lane) {
+                              const float* blocks, const State<G>& pre, const Run<G>& run,
+                              uint32_t head_bits, int t0, int nb, int lane) {
   constexpr int REC = Cfg<G>::REC;
   const int n_chunks = gi.n_chunks, T = gi.T;
   const bool mine = lane < G;   // lane h holds head h
@@ -1216,10 +1418,9 @@ __device__ void resolve_heads(const KernelParams& P, int gidx, int k, const Grou
   const bool finish = !all_after && k == n_chunks - 1;
   const int upto = finish ? nb - 1 : last_rel;
   if (upto >= 0) {
-    State<G> o = pre, t;
+    State<G> o = pre;
     for (int i = 0; i <= upto; ++i) {
-      read_tile<G>(blocks + i * REC, t, lane);
-      merge<G, false>(o, t);
+      step_block<G>(o, run, blocks, i, lane);
       uint32_t here = 0;
 #pragma unroll
       for (int h = 0; h < G; ++h)
@@ -1234,39 +1435,24 @@ __device__ void resolve_heads(const KernelParams& P, int gidx, int k, const Grou
 }
 
 // Phase 2 for one chunk (resolver wavefront).  `blocks` holds the chunk's
-// block records, `aggbuf` the loaders' partial aggregates (nagg of them).
+// block records.
 template <int G, bool PH>
 __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const GroupInfo& gi,
-                              float* blocks, const float* aggbuf, int nagg, int lane) {
+                              const float* blocks, int lane) {
   constexpr int REC = Cfg<G>::REC;
   const int b = gi.b, kvh = gi.kvh, T = gi.T, n_chunks = gi.n_chunks;
   const int t0 = chunk_start(P, k);
   const int nb = min(chunk_start(P, k + 1), T) - t0;
+  const bool last = k == n_chunks - 1;
   const __amdgpu_buffer_rsrc_t rs = record_rsrc(P, gidx);
   const int rec_agg = k * 2 * P.record_floats;          // float offsets in the group's area
   const int rec_inc = rec_agg + P.record_floats;
 
   // the predecessor's flag, read now so that the round trip overlaps the
-  // aggregate fold
+  // aggregate
   const uint64_t prev_flag = k > 0 ? ld_relaxed(P.flags + (int64_t)gidx * P.max_chunks + (k - 1)) : 0ull;
-  // chunk aggregate: w0 (+) (w1 (+) w2) over the loaders' partials, or a
-  // left fold over the blocks when the partials did not fit in LDS
   State<G> agg;
-  if (nagg == kLoaders) {
-    State<G> a1, a2;
-    read_state<G>(aggbuf + 0 * REC, agg, lane);
-    read_state<G>(aggbuf + 1 * REC, a1, lane);
-    read_state<G>(aggbuf + 2 * REC, a2, lane);
-    merge<G, false>(a1, a2);
-    merge<G, false>(agg, a1);
-  } else {
-    State<G> t;
-    state_clear<G>(agg);
-    for (int i = 0; i < nb; ++i) {
-      read_tile<G>(blocks + i * REC, t, lane);
-      merge<G, false>(agg, t);
-    }
-  }
+  aggregate<G>(agg, blocks, nb, lane);
 
   // Softmax prefix.  Chunk 0 has an empty prefix; when chunk k-1 already
   // holds its inclusive state the prefix is that record; otherwise publish
@@ -1274,7 +1460,8 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
   // back to the nearest inclusive state and fold the aggregates after it
   // forward, FW records in flight at a time.  Every path computes the same
   // left fold Agg(0) (+) ... (+) Agg(k-1), so the bits never depend on
-  // timing.
+  // timing.  No chunk follows the last one, so it publishes neither its
+  // aggregate nor its inclusive state.
   constexpr int HPL = Cfg<G>::HPL;
   constexpr int FW = 8 / HPL > 0 ? 8 / HPL : 1;
   int j;
@@ -1290,6 +1477,7 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
     // (compiled for 8 or more heads only: the launches that pass the gate
     // are those of many groups of 8, and the extra code alone measurably
     // slowed the instances for smaller groups)
+    j = -3;
     if (G >= 8 && P.look_first) {
       // a few passes, a short sleep apart: a prefix that completes within
       // them spares this chunk its aggregate record (measured: one pass and
@@ -1299,14 +1487,12 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
         __builtin_amdgcn_s_sleep(8);
         j = lookback_once(P, gidx, k, kAggregate, kInclusive, lane);
       }
-      if (j == -3) {
+    }
+    if (j == -3) {
+      if (!last) {
         publish_state<G>(rs, rec_agg, agg, lane);
         publish(P, gidx, k, kAggregate, lane);
-        j = lookback_scan(P, gidx, k, kAggregate, kInclusive, lane);
       }
-    } else {
-      publish_state<G>(rs, rec_agg, agg, lane);
-      publish(P, gidx, k, kAggregate, lane);
       j = lookback_scan(P, gidx, k, kAggregate, kInclusive, lane);
     }
     if (j == -2) return;
@@ -1321,156 +1507,169 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
   }
   for (int i0 = j + 1; i0 < k; i0 += FW) {
     const int n = min(FW, k - i0);
-    State<G> a[FW];
+    float p[FW][HPL][8];
+    float m[HPL], L[HPL];
+#pragma unroll
+    for (int kk = 0; kk < HPL; ++kk) {
+      int h = (lane >> 4) + 4 * kk;
+      if (h >= G) h = 0;
+      const int c = lane & 15, at = (i0 + min(c, n - 1)) * 2 * P.record_floats + G * kD + h;
+      m[kk] = ld_record(rs, at);
+      L[kk] = ld_record(rs, at + G);
+      if (c >= n) L[kk] = 0.f;
+    }
 #pragma unroll
     for (int u = 0; u < FW; ++u)
-      if (u < n) fetch_state<G>(rs, (i0 + u) * 2 * P.record_floats, a[u], lane);
+#pragma unroll
+      for (int kk = 0; kk < HPL; ++kk)
+        if (u < n) fetch_output<G>(rs, (i0 + u) * 2 * P.record_floats, kk, lane, p[u][kk]);
+    Run<G> run;
+#pragma unroll
+    for (int kk = 0; kk < HPL; ++kk) run_factors<G>(run, kk, pre.L[kk] > 0.f ? pre.m[kk] : kNegInf, m[kk], L[kk]);
 #pragma unroll
     for (int u = 0; u < FW; ++u)
-      if (u < n) merge<G, false>(pre, a[u]);
+      if (u < n) {
+        float d[8];
+#pragma unroll
+        for (int kk = 0; kk < HPL; ++kk) run_step<G>(pre, run, kk, u, lane, p[u][kk], d);
+      }
+#pragma unroll
+    for (int kk = 0; kk < HPL; ++kk) pre.m[kk] = row_lane(run.m[kk], 15, lane);
   }
   // this chunk's inclusive state, published before the replay: the next
   // chunks wait for it (measured: raising its flag only after the replay's
   // first blocks, to overlap the stores' completion, was 0.5 % slower)
-  {
+  if (!last || P.no_detector) {
     State<G> inc = pre;
-    merge<G, false>(inc, agg);
-    publish_state<G>(rs, rec_inc, inc, lane);
-    publish(P, gidx, k, kInclusive, lane);
-    if (P.no_detector) {
-      // no stability test (the detector-free baseline): later chunks need
-      // only the inclusive state, and the last chunk holds the output
-      if (k == n_chunks - 1) write_outputs<G>(P, b, kvh, inc, T, lane);
-      return;
+    merge<G>(inc, agg);
+    if (!last) {
+      publish_state<G>(rs, rec_inc, inc, lane);
+      publish(P, gidx, k, kInclusive, lane);
+    } else {
+      // no stability test (the detector-free baseline): the last chunk
+      // holds the output
+      write_outputs<G>(P, b, kvh, inc, T, lane);
     }
+    if (P.no_detector) return;
   }
 
-  // Replay the chunk's blocks from the prefix with the stability test.
-  // Blocks go in batches of NB: the merges run in order (each needs the
-  // state after the previous block) and leave per-lane partial sums of
-  // |d|^2 and o(t-1).d per head; the row reductions of the whole batch then
-  // run together, and |o(t)|^2 follows as |o(t-1)|^2 + 2 o(t-1).d + |d|^2.
+  // Replay the chunk's blocks from the prefix with the stability test.  The
+  // steps run in order (each needs the state after the previous block); the
+  // row sums of |d|^2 and o(t-1).d of block i stay in lane c = i of the
+  // head's row with |o(t-1)|^2, and |o(t)|^2 follows as
+  // |o(t-1)|^2 + 2 o(t-1).d + |d|^2.  The verdicts of all blocks and heads
+  // are then taken at once, lane (r, c) for block c of head r + 4k.  (One
+  // verdict after the other and merges with their exponentials inside took
+  // 2.0 us for 3 blocks and 5.0 for 9 at g = 4, 7.7 for 9 at g = 8.)
   // The probe weights (Sec. 3.2, x = P o: 1 on the coordinates the test
   // looks at, every probe_stride-th of the head dimension, 0 elsewhere)
   // multiply the partial sums only when the probe is a subsample; this lane
   // holds coordinates 8*(lane&15) .. +7.
-  constexpr int NB = 8 / HPL > 0 ? 8 / HPL : 1;
   uint32_t stable_bits = 0;
   uint32_t head_bits = 0;   // per-head mode: lane h < G, head h's stable blocks
   State<G> s = pre;   // after the replay: the state after the chunk's last block
+  Run<G> run;
   {
+    const int c = lane & 15;
     const bool full_probe = P.probe_stride == 1;
+    const bool on_acc = P.scale_of_accumulator != 0;
     float pw[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e)
-      pw[e] = ((8 * (lane & 15) + e) & (P.probe_stride - 1)) == 0 ? 1.f : 0.f;
-    // |x|^2 per head slot of the state before the next block
-    float n_prev[HPL];
+    for (int e = 0; e < 8; ++e) pw[e] = ((8 * c + e) & (P.probe_stride - 1)) == 0 ? 1.f : 0.f;
+    float n_prev[HPL];                              // |x|^2 of the state before the next block
+    float acc_dx[HPL];
+    float q0[HPL], q1[HPL], qdd[HPL], qod[HPL];     // lane (r, c): block c's |x(t-1)|^2, |x(t)|^2, |d|^2, x.d
 #pragma unroll
     for (int kk = 0; kk < HPL; ++kk) {
+      float m, L;
+      read_masses<G>(blocks, nb, kk, lane, m, L);
+      run_factors<G>(run, kk, pre.L[kk] > 0.f ? pre.m[kk] : kNegInf, m, L);
       float n0 = 0.f;
 #pragma unroll
       for (int e = 0; e < 8; ++e) n0 = __builtin_fmaf(full_probe ? s.o[kk][e] : s.o[kk][e] * pw[e], s.o[kk][e], n0);
       n_prev[kk] = row_sum(n0);
+      q0[kk] = q1[kk] = qdd[kk] = qod[kk] = acc_dx[kk] = 0.f;
     }
-    const bool on_acc = P.scale_of_accumulator != 0;
-    for (int i0 = 0; i0 < nb; i0 += NB) {
-      float pdd[NB][HPL], pod[NB][HPL], pdx[NB][HPL];
+    for (int i = 0; i < nb; ++i) {
 #pragma unroll
-      for (int u = 0; u < NB; ++u) {
+      for (int kk = 0; kk < HPL; ++kk) {
+        float p[8], d[8], o0[8];
+        read_output<G>(blocks + i * REC, kk, lane, p);
+        const float L0 = s.L[kk];
 #pragma unroll
-        for (int kk = 0; kk < HPL; ++kk) pdd[u][kk] = pod[u][kk] = pdx[u][kk] = 0.f;
-        const int i = i0 + u;
-        if (i < nb) {
-          State<G> blkst;
-          read_tile<G>(blocks + i * REC, blkst, lane);
-          float old_o[HPL][8], old_L[HPL];
+        for (int e = 0; e < 8; ++e) o0[e] = s.o[kk][e];
+        run_step<G>(s, run, kk, i, lane, p, d);
+        float dd = 0.f, od = 0.f;
+        if (full_probe) {
 #pragma unroll
-          for (int kk = 0; kk < HPL; ++kk) {
-            old_L[kk] = s.L[kk];
-#pragma unroll
-            for (int e = 0; e < 8; ++e) old_o[kk][e] = s.o[kk][e];
+          for (int e = 0; e < 8; ++e) {
+            dd = __builtin_fmaf(d[e], d[e], dd);
+            od = __builtin_fmaf(o0[e], d[e], od);
           }
-          float d[HPL][8];
-          merge<G, true>(s, blkst, d);
+        } else {
 #pragma unroll
-          for (int kk = 0; kk < HPL; ++kk) {
-            float dd = 0.f, od = 0.f, dx2 = 0.f;
-            if (full_probe) {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                dd = __builtin_fmaf(d[kk][e], d[kk][e], dd);
-                od = __builtin_fmaf(old_o[kk][e], d[kk][e], od);
-              }
-            } else {
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                dd = __builtin_fmaf(d[kk][e] * pw[e], d[kk][e], dd);
-                od = __builtin_fmaf(old_o[kk][e] * pw[e], d[kk][e], od);
-              }
-            }
-            if (on_acc) {
-              // change of the unnormalised accumulator L o, each side in its
-              // own max reference (L is the mass relative to the running max)
-#pragma unroll
-              for (int e = 0; e < 8; ++e) {
-                const float dx = __fsub_rn(__fmul_rn(s.L[kk], s.o[kk][e]), __fmul_rn(old_L[kk], old_o[kk][e]));
-                dx2 = __builtin_fmaf(dx * pw[e], dx, dx2);
-              }
-            }
-            pdd[u][kk] = dd;
-            pod[u][kk] = od;
-            pdx[u][kk] = dx2;
+          for (int e = 0; e < 8; ++e) {
+            dd = __builtin_fmaf(d[e] * pw[e], d[e], dd);
+            od = __builtin_fmaf(o0[e] * pw[e], d[e], od);
           }
+        }
+        dd = row_sum(dd);
+        od = row_sum(od);
+        const float n0 = n_prev[kk], n1 = __fadd_rn(__fadd_rn(n0, __fmul_rn(2.f, od)), dd);   // |x(t)|^2
+        n_prev[kk] = n1;
+        if (c == i) {
+          q0[kk] = n0;
+          q1[kk] = n1;
+          qdd[kk] = dd;
+          qod[kk] = od;
+        }
+        if (on_acc) {
+          // change of the unnormalised accumulator L o, each side in its
+          // own max reference (L is the mass relative to the running max):
+          // it takes the place of |d|^2 in the magnitude test below
+          float dx2 = 0.f;
+#pragma unroll
+          for (int e = 0; e < 8; ++e) {
+            const float dx = __fsub_rn(__fmul_rn(s.L[kk], s.o[kk][e]), __fmul_rn(L0, o0[e]));
+            dx2 = __builtin_fmaf(dx * pw[e], dx, dx2);
+          }
+          dx2 = row_sum(dx2);
+          if (c == i) acc_dx[kk] = dx2;
         }
       }
-#pragma unroll
-      for (int u = 0; u < NB; ++u)
-#pragma unroll
-        for (int kk = 0; kk < HPL; ++kk) {
-          pdd[u][kk] = row_sum(pdd[u][kk]);
-          pod[u][kk] = row_sum(pod[u][kk]);
-          if (on_acc) pdx[u][kk] = row_sum(pdx[u][kk]);
-        }
-#pragma unroll
-      for (int u = 0; u < NB; ++u) {
-        const int i = i0 + u;
-        if (i >= nb) break;
-        bool ok = true;
-#pragma unroll
-        for (int kk = 0; kk < HPL; ++kk) {
-          const float n0 = n_prev[kk], dd = pdd[u][kk], od = pod[u][kk];
-          const float n1 = __fadd_rn(__fadd_rn(n0, __fmul_rn(2.f, od)), dd);   // |x(t)|^2
-          n_prev[kk] = n1;
-          // Eq. (2) on the probe: d_scale = |P d| (or the change of P L o);
-          // d_direction = 1 - cos(P o_new, P o_old)
-          const float d_scale = fast_sqrt(on_acc ? pdx[u][kk] : dd);
-          const float nn = __fmul_rn(fast_sqrt(n1), fast_sqrt(n0));
-          const float dot = __fadd_rn(n0, od);
-          float d_dir;
-          if (dot > 0.f) {
-            const float num = fmaxf(__fsub_rn(__fmul_rn(n0, dd), __fmul_rn(od, od)), 0.f);
-            d_dir = __fmul_rn(num, fast_rcp(__fmul_rn(nn, __fadd_rn(nn, dot))));
-          } else {
-            d_dir = __fsub_rn(1.f, __fmul_rn(dot, fast_rcp(nn)));
-          }
-          const bool st = (n0 > 0.f) && (n1 > 0.f) && (d_scale < P.tau) && (d_dir < P.phi);
-          if (slot_valid<G>(lane, kk) && !st) ok = false;
-          if (PH) {
-            // lane h < G collects head h's verdicts: head h sits in slot
-            // h / 4 of the lanes of row h % 4
-            const uint64_t bal = __ballot(st);
-            if (lane < G && (lane >> 2) == kk) head_bits |= (uint32_t)((bal >> (16 * (lane & 3))) & 1ull) << i;
-          }
-        }
-        const bool all_ok = __all(ok);
-        stable_bits |= (all_ok ? 1u : 0u) << i;
-      }
     }
+#pragma unroll
+    for (int kk = 0; kk < HPL; ++kk) s.m[kk] = row_lane(run.m[kk], 15, lane);
+    uint32_t all = 0xffffu;
+#pragma unroll
+    for (int kk = 0; kk < HPL; ++kk) {
+      const float n0 = q0[kk], n1 = q1[kk], dd = qdd[kk], od = qod[kk];
+      // Eq. (2) on the probe: d_scale = |P d| (or the change of P L o);
+      // d_direction = 1 - cos(P o_new, P o_old)
+      const float d_scale = fast_sqrt(on_acc ? acc_dx[kk] : dd);
+      const float nn = __fmul_rn(fast_sqrt(n1), fast_sqrt(n0));
+      const float dot = __fadd_rn(n0, od);
+      float d_dir;
+      if (dot > 0.f) {
+        const float num = fmaxf(__fsub_rn(__fmul_rn(n0, dd), __fmul_rn(od, od)), 0.f);
+        d_dir = __fmul_rn(num, fast_rcp(__fmul_rn(nn, __fadd_rn(nn, dot))));
+      } else {
+        d_dir = __fsub_rn(1.f, __fmul_rn(dot, fast_rcp(nn)));
+      }
+      const bool st = (n0 > 0.f) && (n1 > 0.f) && (d_scale < P.tau) && (d_dir < P.phi);
+      // bits 16 r + c: block c of head r + 4k
+      const uint64_t bal = __ballot(st);
+      if (PH && lane < G && (lane >> 2) == kk) head_bits = (uint32_t)(bal >> (16 * (lane & 3))) & 0xffffu;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (r + 4 * kk < G) all &= (uint32_t)(bal >> (16 * r));
+    }
+    stable_bits = all & ((1u << nb) - 1u);
+    head_bits &= (1u << nb) - 1u;
   }
 
   if constexpr (PH) {
-    resolve_heads<G>(P, gidx, k, gi, blocks, pre, head_bits, t0, nb, lane);
+    resolve_heads<G>(P, gidx, k, gi, blocks, pre, run, head_bits, t0, nb, lane);
     return;
   }
   // stability summary of this chunk (entering run 0)
@@ -1499,7 +1698,7 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
   // A chunk whose first block is unstable and whose own run never reaches
   // the patience cannot hold the stop, whatever run it enters with: unless
   // it is the last chunk (which writes the untruncated result) it is done.
-  if (sm.lead == 0 && sm.fis < 0 && k != n_chunks - 1) return;
+  if (sm.lead == 0 && sm.fis < 0 && !last) return;
 
   // entering stability state, then this chunk's own
   StabState x;
@@ -1513,13 +1712,10 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
   if (!stopped_before && y.stopped) {
     // the stop lies in this chunk: o(t*) again from the prefix, by the same
     // merges as the replay (the same bits)
-    State<G> o = pre, t;
-    for (int i = 0; i < y.stop_t - t0; ++i) {
-      read_tile<G>(blocks + i * REC, t, lane);
-      merge<G, false>(o, t);
-    }
+    State<G> o = pre;
+    for (int i = 0; i < y.stop_t - t0; ++i) step_block<G>(o, run, blocks, i, lane);
     write_outputs<G>(P, b, kvh, o, y.stop_t, lane);
-  } else if (!y.stopped && k == n_chunks - 1) {
+  } else if (!y.stopped && last) {
     write_outputs<G>(P, b, kvh, s, T, lane);
   }
 }
@@ -1530,10 +1726,10 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
 // turn; wavefront 0 resolves earlier chunks meanwhile.  A chunk is claimed
 // only once a buffer is free, and every wait targets a chunk claimed
 // earlier, so the launch always makes progress.
-template <int G, bool PH>
+template <int G, bool PH, bool WIDE>
 // (groups of 16 heads need the bound to keep two workgroups per CU; for
 // the smaller groups the compiler's own choice was faster)
-__global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(const KernelParams P) {
+__global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelParams P) {
   // the dynamic buffers must start 16-byte aligned (128-bit LDS accesses):
   // the static block below is a multiple of 16 bytes
   extern __shared__ __align__(16) float smem[];
@@ -1547,8 +1743,7 @@ __global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(c
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   const int n_groups = P.batch * P.num_kv_heads;
   const int CT = P.chunk_recs_lds;
-  const int nagg = P.loader_partials;
-  const int slot_floats = (CT + nagg) * REC;
+  const int slot_floats = CT * REC;
   const int n_slots = P.n_slots;
   // V staging buffers of the loaders after the chunk buffers (16-byte aligned)
   uint16_t* vbuf_all = reinterpret_cast<uint16_t*>(smem + ((n_slots * slot_floats + 3) & ~3));
@@ -1570,13 +1765,13 @@ __global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(c
         __builtin_amdgcn_s_sleep(1);
       }
       if (st == kSlotEnd) return;
-      const int gidx = lds_ld(&s_meta[slot][kMetaGroup]);
-      const int k = lds_ld(&s_meta[slot][kMetaChunk]);
+      const int gidx = lds_uniform(&s_meta[slot][kMetaGroup]);
+      const int k = lds_uniform(&s_meta[slot][kMetaChunk]);
       if (!lds_ld(&s_meta[slot][kMetaAbort])) {
         float* base = smem + slot * slot_floats;
-        const GroupInfo gi = group_info_raw(P, gidx, lds_ld(&s_meta[slot][kMetaLen]),
-                                            lds_ld(&s_meta[slot][kMetaListLen]));
-        resolve_chunk<G, PH>(P, gidx, k, gi, base, base + CT * REC, nagg, lane);
+        const GroupInfo gi = group_info_raw(P, gidx, lds_uniform(&s_meta[slot][kMetaLen]),
+                                            lds_uniform(&s_meta[slot][kMetaListLen]));
+        resolve_chunk<G, PH>(P, gidx, k, gi, base, lane);
       }
       wave_lds_sync();
       if (lane == 0) lds_st(&s_meta[slot][kMetaState], kSlotFree);
@@ -1667,10 +1862,10 @@ __global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(c
       __builtin_amdgcn_s_sleep(1);
     }
     if (st == kSlotEnd) return;
-    const int gidx = lds_ld(&s_meta[slot][kMetaGroup]);
-    const int k = lds_ld(&s_meta[slot][kMetaChunk]);
-    const GroupInfo gi = group_info_raw(P, gidx, lds_ld(&s_meta[slot][kMetaLen]),
-                                        lds_ld(&s_meta[slot][kMetaListLen]));
+    const int gidx = lds_uniform(&s_meta[slot][kMetaGroup]);
+    const int k = lds_uniform(&s_meta[slot][kMetaChunk]);
+    const GroupInfo gi = group_info_raw(P, gidx, lds_uniform(&s_meta[slot][kMetaLen]),
+                                        lds_uniform(&s_meta[slot][kMetaListLen]));
     const int t0 = chunk_start(P, k);
     const int nb = min(chunk_start(P, k + 1), gi.T) - t0;
     const int tpb = P.tiles_per_block;
@@ -1732,7 +1927,7 @@ __global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(c
         const int tok0 = __builtin_amdgcn_readlane(my_tok0, 4 * m);
         const int pg[4] = {__builtin_amdgcn_readlane(my_page, 4 * m), __builtin_amdgcn_readlane(my_page, 4 * m + 1),
                            __builtin_amdgcn_readlane(my_page, 4 * m + 2), __builtin_amdgcn_readlane(my_page, 4 * m + 3)};
-        compute_tile<G>(P, gi.kvh, gi.L, tok0, pg, qa,
+        compute_tile<G, WIDE>(P, gi.kvh, gi.L, tok0, pg, qa,
                         P.v_in_record ? reinterpret_cast<uint16_t*>(blocks + i * REC) : vbuf,
                         blocks + i * REC, j > 0);
         if (stop_word_before(sw, P.epoch, k)) {
@@ -1744,15 +1939,6 @@ __global__ void __launch_bounds__(kThreads, G >= 16 ? 2 : 1) art_decode_kernel(c
     wave_lds_sync();
     if (aborted) {
       if (lane == 0) lds_st(&s_meta[slot][kMetaAbort], 1);
-    } else if (nagg == kLoaders) {
-      // this loader's blocks folded in order: a partial aggregate
-      State<G> wagg, t;
-      state_clear<G>(wagg);
-      for (int i = lw; i < nb; i += kLoaders) {
-        read_tile<G>(blocks + i * REC, t, lane);
-        merge<G, false>(wagg, t);
-      }
-      write_state<G>(blocks + CT * REC + lw * REC, wagg, lane);
     }
     wave_lds_sync();
     stress_delay(P, gidx, k, 13 + lw);
@@ -1769,15 +1955,15 @@ __global__ void fill_zero_kernel(uint32_t* p, size_t n_words) {
   for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_words; i += stride) p[i] = 0u;
 }
 
-template <int G, bool PH>
-int launch_g(const Plan& plan, const KernelParams& params, hipStream_t stream) {
+template <int G, bool PH, bool WIDE>
+int launch_w(const Plan& plan, const KernelParams& params, hipStream_t stream) {
   const int64_t work = (int64_t)plan.n_groups * plan.max_chunks;
   if (work <= 0) return (int)hipSuccess;
   int dev = 0, cus = 0, per_cu = 0;
   hipError_t e = hipGetDevice(&dev);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
   if (e == hipSuccess)
-    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, art_decode_kernel<G, PH>, kThreads, plan.lds_bytes);
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, art_decode_kernel<G, PH, WIDE>, kThreads, plan.lds_bytes);
   if (e != hipSuccess) return (int)e;
   if (per_cu < 1) per_cu = 1;
   // As many workgroups as the chip holds, but at most 32 per group (and
@@ -1793,10 +1979,15 @@ int launch_g(const Plan& plan, const KernelParams& params, hipStream_t stream) {
   // bits either way.
   KernelParams p = params;
   p.look_first = grid * plan.slots <= (int64_t)8 * plan.n_groups ? 1 : 0;
-  auto kernel = art_decode_kernel<G, PH>;
+  auto kernel = art_decode_kernel<G, PH, WIDE>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads),
                      plan.lds_bytes, stream, p);
   return (int)hipGetLastError();
+}
+
+template <int G, bool PH>
+int launch_g(const Plan& plan, const KernelParams& params, hipStream_t stream) {
+  return params.wide ? launch_w<G, PH, true>(plan, params, stream) : launch_w<G, PH, false>(plan, params, stream);
 }
 
 }  // namespace
