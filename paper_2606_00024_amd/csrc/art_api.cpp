@@ -105,7 +105,7 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     if (t_cap >= (int64_t(1) << 19)) return ART_ERR_UNSUPPORTED;
     const int64_t n_groups = (int64_t)s->batch * s->num_kv_heads;
 
-    // LDS of a workgroup: two or three chunk buffers of C*tpb tile records
+    // LDS of a workgroup: two chunk buffers of C*tpb tile records
     // and three V staging buffers: half tiles (32 rows of 288 bytes) for groups
     // of up to 4 heads, quarter tiles (4 KiB) for 8 or more.  A record of 8
     // or more heads holds 4 KiB of outputs, so when every block is one tile
@@ -116,9 +116,9 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     const bool v_in_record = g >= 8 && tpb == 1;
     const size_t pbuf_bytes = v_in_record ? 0 : (g >= 8 ? (size_t)3 * 4096 : (size_t)3 * 32 * 288) + 16;
     const size_t lds_cap = 78 * 1024;
-    auto lds_for = [&](int blocks, int slots) { return slots * (size_t)blocks * rec_bytes + pbuf_bytes; };
+    auto lds_for = [&](int blocks) { return art::kChunkSlots * (size_t)blocks * rec_bytes + pbuf_bytes; };
     int c_max = art::kMaxChunkBlocks;
-    while (c_max > 0 && lds_for(c_max, 2) > lds_cap) --c_max;
+    while (c_max > 0 && lds_for(c_max) > lds_cap) --c_max;
     // a loader streams at most kMaxChunkTiles tiles of a chunk
     while (c_max > 1 && (c_max + 2) / 3 * tpb > art::kMaxChunkTiles) --c_max;
     if (c_max < 1) return ART_ERR_UNSUPPORTED;
@@ -162,10 +162,7 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     p->t_cap = (int32_t)t_cap;
     p->record_floats = (g * art::kHeadDim + 2 * g + 63) / 64 * 64;
     p->v_in_record = v_in_record ? 1 : 0;
-    // (a third buffer was measured: it lets loaders run further past a
-    // stop and gains nothing elsewhere)
-    p->slots = 2;
-    p->lds_bytes = lds_for(C, p->slots);
+    p->lds_bytes = lds_for(C);
 
     art::WorkspaceLayout& w = p->ws;
     size_t off = 0;
@@ -244,7 +241,6 @@ art_status enqueue_decode(const Plan& plan, const art_decode_shape* shape,
     k.lead_chunks = plan.lead_chunks;
     k.lead_blocks = plan.lead_blocks;
     k.t_cap = plan.t_cap;
-    k.n_slots = plan.slots;
     {
         // the work list covers the longest traversal this call can have
         const int64_t cap_tokens = (int64_t)shape->max_pages_per_seq * shape->page_size;
@@ -255,7 +251,6 @@ art_status enqueue_decode(const Plan& plan, const art_decode_shape* shape,
         k.work_chunks = (int32_t)chunks_for(t_eff, plan.chunk_blocks, plan.lead_chunks, plan.lead_blocks);
     }
     k.record_floats = plan.record_floats;
-    k.chunk_recs_lds = plan.chunk_blocks;
     k.v_in_record = plan.v_in_record;
     k.q = static_cast<const uint16_t*>(q);
     k.k = static_cast<const uint16_t*>(k_cache);

@@ -15,6 +15,10 @@ constexpr int kWaves = 4;       // wavefronts per workgroup
 constexpr int kThreads = 64 * kWaves;
 constexpr int kMaxChunkTiles = 16;   // tiles one loader streams per chunk (and per block)
 constexpr int kMaxChunkBlocks = 16;  // blocks per chunk
+// Chunk buffers in LDS: one is resolved while the next is loaded.  (A third
+// was measured: it lets loaders run further past a stop and gains nothing
+// elsewhere.)
+constexpr int kChunkSlots = 2;
 // Work-list indices live in the low 24 bits of the queue word; a launch
 // hands out at most its list length plus one final index per workgroup.
 constexpr int kQueueBits = 24;
@@ -57,7 +61,6 @@ struct Plan {
     int32_t t_cap;           // traversal length bound per group
     int32_t record_floats;   // floats per aggregate / inclusive record
     int32_t v_in_record;     // see KernelParams
-    int32_t slots;           // chunk buffers in LDS (2 or 3)
     size_t lds_bytes;        // dynamic LDS per workgroup
     WorkspaceLayout ws;
 };
@@ -80,8 +83,6 @@ struct KernelParams {
     int32_t tiles_per_block, chunk_blocks, max_chunks, t_cap, record_floats;
     int32_t lead_chunks, lead_blocks;  // the first lead_chunks chunks hold lead_blocks blocks
     int32_t work_chunks;     // chunk rows of the work list (<= max_chunks)
-    int32_t chunk_recs_lds;  // block records per LDS chunk buffer
-    int32_t n_slots;         // chunk buffers in LDS (2 or 3)
     int32_t v_in_record;     // 1: V is staged in the LDS record being written (no staging buffers)
     int32_t wide;            // 1: rows of K or of V lie 8 MiB or more apart (64-bit lane addresses)
     int32_t look_first;      // 1: a chunk looks back once before publishing its aggregate (set at launch)

@@ -62,8 +62,22 @@ namespace {
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kNegInf = -__builtin_inff();
+
+// The kernel's parameters, read where they are used from the kernel argument
+// segment through the scalar cache.  fresh() hides the pointer's origin from
+// the compiler: it then loads a phase's fields in that phase, instead of
+// holding all of them (about 60 registers' worth, with what it derives from
+// them) in scalar registers across the whole kernel.  Held so, 140 of them
+// were spilled to lanes of vector registers, and 1170 of the kernel's 3600
+// instructions (g = 4) were v_readlane to fetch them back.
+typedef const __attribute__((address_space(4))) KernelParams Params;
+__device__ __forceinline__ Params* fresh(Params* p) {
+  __asm__ __volatile__("" : "+s"(p));
+  return p;
+}
 constexpr int kD = kHeadDim;
 
 __device__ __forceinline__ float bf_lo(uint32_t w) { return __uint_as_float(w << 16); }
@@ -156,6 +170,17 @@ __device__ __forceinline__ void wave_lds_sync() {
   __asm__ __volatile__("" ::: "memory");
 }
 
+// The same ordering without the wait, where only this wave touches the
+// memory: the LDS unit executes one wavefront's operations in the order they
+// were issued, so a read issued after a write of any lane of the wave sees
+// it, and a write issued after a read cannot overtake it.  Only the compiler
+// has to be kept from reordering them.
+__device__ __forceinline__ void wave_lds_order() {
+  __asm__ __volatile__("" ::: "memory");
+  __builtin_amdgcn_wave_barrier();
+  __asm__ __volatile__("" ::: "memory");
+}
+
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // single hardware instructions (about 1 ulp): the same bits wherever used
 __device__ __forceinline__ float fast_rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -226,13 +251,11 @@ __device__ __forceinline__ uint32_t flag_payload(uint64_t v) { return (uint32_t)
 // call but does not end this one.)
 constexpr uint32_t kTimeoutStatus = 6u;   // ART_ERR_DEVICE_TIMEOUT
 constexpr uint32_t kErrPollEvery = 16u;
-template <typename Params>
-__device__ __forceinline__ void raise_timeout(const Params& P) {
+__device__ __forceinline__ void raise_timeout(Params& P) {
   __hip_atomic_store(P.error_word, (P.epoch << 8) | kTimeoutStatus, __ATOMIC_RELAXED,
                      __HIP_MEMORY_SCOPE_AGENT);
 }
-template <typename Params>
-__device__ __forceinline__ bool launch_failed(const Params& P) {
+__device__ __forceinline__ bool launch_failed(Params& P) {
   return (ld_relaxed(P.error_word) >> 8) == P.epoch;
 }
 // Race stress (the build with ART_RACE_STRESS defined, a test build only):
@@ -241,8 +264,7 @@ __device__ __forceinline__ bool launch_failed(const Params& P) {
 // over, keyed by the call, the group, the chunk and the site, so that the
 // look-back's producers and consumers meet in orders a plain run rarely
 // shows.  Delays only stretch time: every wait stays bounded.
-template <typename Params>
-__device__ __forceinline__ void stress_delay(const Params& P, int gidx, int k, int site) {
+__device__ __forceinline__ void stress_delay(Params& P, int gidx, int k, int site) {
 #ifdef ART_RACE_STRESS
   uint32_t h = (uint32_t)P.epoch * 0x9E3779B1u ^ (uint32_t)gidx * 0x85EBCA77u ^
                (uint32_t)k * 0xC2B2AE3Du ^ (uint32_t)site * 0x27D4EB2Fu;
@@ -257,8 +279,7 @@ __device__ __forceinline__ void stress_delay(const Params& P, int gidx, int k, i
 }
 
 // The give-up test of one poll of a wait loop (spin counts the polls made).
-template <typename Params>
-__device__ __forceinline__ bool wait_expired(const Params& P, uint32_t spin) {
+__device__ __forceinline__ bool wait_expired(Params& P, uint32_t spin) {
   if (spin >= P.spin_limit) {
     raise_timeout(P);
     return true;
@@ -449,7 +470,7 @@ __device__ __forceinline__ void aggregate(State<G>& s, const float* blocks, int 
 constexpr int kCoherent = 16;  // buffer cache policy: sc1
 constexpr int kLookFirstPasses = 5;  // look-back passes before a chunk publishes its aggregate
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t record_rsrc(const KernelParams& P, int gidx) {
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t record_rsrc(Params& P, int gidx) {
   const float* base = P.records + (int64_t)gidx * P.max_chunks * 2 * P.record_floats;
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0,
                                            P.max_chunks * 2 * P.record_floats * 4, 0x00020000);
@@ -509,7 +530,7 @@ __device__ __forceinline__ void fetch_state(__amdgpu_buffer_rsrc_t rs, int rec_o
 
 // ---- phase 1: one 64-token tile on one wavefront ---------------------------
 template <int G>
-__device__ __forceinline__ void load_q(const KernelParams& P, int b, int kvh, int lane, bf16x8 (&qa)[4]) {
+__device__ __forceinline__ void load_q(Params& P, int b, int kvh, int lane, bf16x8 (&qa)[4]) {
   const int h = lane & (Cfg<G>::COLS - 1);
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
@@ -523,7 +544,7 @@ __device__ __forceinline__ void load_q(const KernelParams& P, int b, int kvh, in
   }
 }
 
-__device__ __forceinline__ int clamp_page(const KernelParams& P, int b, int tok) {
+__device__ __forceinline__ int clamp_page(Params& P, int b, int tok) {
   int pg = P.page_table[(int64_t)b * P.max_pages + (tok >> P.page_shift)];
   pg = pg < 0 ? 0 : pg;
   return pg >= P.num_pages ? P.num_pages - 1 : pg;
@@ -563,7 +584,7 @@ __device__ __forceinline__ int vstage_off(int row, int piece) {
 // the block (accumulate) is folded into it: both parts rescaled to the
 // larger running max and the combined mass, in tile order.
 template <int G, bool WIDE>
-__device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, const int (&pg)[4],
+__device__ void compute_tile(Params& P, int kvh, int L, int tok0, const int (&pg)[4],
                              const bf16x8 (&qa)[4], uint16_t* __restrict__ vbuf,
                              float* __restrict__ rec, bool accumulate) {
   const int lane = threadIdx.x & 63;
@@ -701,10 +722,15 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
 
   // A operands of the two 32-token K-steps c: element e of lane (lo, g) is
   // p of head lo at token 16(2c + e/4) + 4g + e%4, in three bf16 parts (hi +
-  // mid + lo carries 24 significant bits).  The groups that other copies
-  // hold come from lanes lo + COLS, lo + 2 COLS, ... of the row; the rows of
-  // A past the last head then hold other lanes' values, which only reach
-  // accumulator rows that nothing reads.
+  // mid + lo carries 24 significant bits).  Fewer than 16 heads leave rows of
+  // A free: up to four heads put the parts in rows h, 4 + h, 8 + h, 12 + h of
+  // one operand (the last two hold half of lo each, exactly, so that no row
+  // multiplies V by zeros), eight put hi and mid in rows h and 8 + h of one
+  // and the halves of lo in those of another.  One product (two) then does
+  // the work of three, and the parts' sums are added across the accumulator
+  // rows at the end.  The parts reach their rows through the wave's staging
+  // memory: row m holds its tokens as [g][n][4], 128 bytes.
+  constexpr int NP = G > 8 ? 3 : G > 4 ? 2 : 1;
   uint32_t own[NS][3][2];
 #pragma unroll
   for (int i = 0; i < NS; ++i)
@@ -717,26 +743,37 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
         own[i][j][e] = w;
         a0 = a0 - bf_lo(w);
         a1 = a1 - bf_hi(w);
+        if (G <= 8 && j == 1) {
+          a0 = 0.5f * a0;
+          a1 = 0.5f * a1;
+        }
       }
     }
-  bf16x8 a[2][3];
+  bf16x8 a[2][NP];
+  if constexpr (G > 8) {
 #pragma unroll
-  for (int j = 0; j < 3; ++j)
+    for (int j = 0; j < 3; ++j)
+#pragma unroll
+      for (int c = 0; c < 2; ++c)
+        a[c][j] = __builtin_bit_cast(
+            bf16x8, u32x4{own[2 * c][j][0], own[2 * c][j][1], own[2 * c + 1][j][0], own[2 * c + 1][j][1]});
+  } else {
+    const int h = lo & (COLS - 1);
+#pragma unroll
+    for (int j = 0; j < (G > 4 ? 3 : 4); ++j)
+#pragma unroll
+      for (int i = 0; i < NS; ++i)
+        *reinterpret_cast<u32x2*>(vbuf + (COLS * j + h) * 64 + g * 16 + 4 * (REP * i + u)) =
+            u32x2{own[i][j < 3 ? j : 2][0], own[i][j < 3 ? j : 2][1]};
+    wave_lds_order();
 #pragma unroll
     for (int c = 0; c < 2; ++c) {
-      u32x4 w;
-      if constexpr (REP == 1) {
-        w = u32x4{own[2 * c][j][0], own[2 * c][j][1], own[2 * c + 1][j][0], own[2 * c + 1][j][1]};
-      } else if constexpr (REP == 2) {
-        w = u32x4{own[c][j][0], own[c][j][1], dpp_u<kRowRor8>(own[c][j][0]), dpp_u<kRowRor8>(own[c][j][1])};
-      } else if (c == 0) {
-        w = u32x4{own[0][j][0], own[0][j][1], dpp_u<kRowRor12>(own[0][j][0]), dpp_u<kRowRor12>(own[0][j][1])};
-      } else {
-        w = u32x4{dpp_u<kRowRor8>(own[0][j][0]), dpp_u<kRowRor8>(own[0][j][1]),
-                  dpp_u<kRowRor4>(own[0][j][0]), dpp_u<kRowRor4>(own[0][j][1])};
-      }
-      a[c][j] = __builtin_bit_cast(bf16x8, w);
+      a[c][0] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vbuf + lo * 64 + g * 16 + 8 * c));
+      if constexpr (NP == 2)
+        a[c][NP - 1] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(vbuf + (16 + h) * 64 + g * 16 + 8 * c));
     }
+    wave_lds_order();  // the parts are read before V takes the memory
+  }
 
   // P.V over the two halves of the tile.  B for K-step c and dims
   // 16d .. 16d+15: lane (lo, g) needs V[token of element e][16d + lo]; in
@@ -758,7 +795,7 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
 #pragma unroll
         for (int i = 0; i < 4; ++i)
           *reinterpret_cast<u32x4*>(vbuf + vstage_off(4 * i + g, lo)) = vr[8 * c + 4 * qh + i];
-        wave_lds_sync();
+        wave_lds_order();
 #pragma unroll
         for (int d = 0; d < 8; ++d) {
           const v4i16 r = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -769,10 +806,10 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
           } else {
             const bf16x8 b = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0[d], r, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-            for (int j = 0; j < 3; ++j) acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c][j], b, acc[d], 0, 0, 0);
+            for (int j = 0; j < NP; ++j) acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c][j], b, acc[d], 0, 0, 0);
           }
         }
-        wave_lds_sync();  // the reads of this quarter complete before the next one is written
+        wave_lds_order();  // the reads of this quarter come before the next one's writes
       }
     }
   } else {
@@ -783,7 +820,7 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
 #pragma unroll
       for (int i = 0; i < 8; ++i)
         *reinterpret_cast<u32x4*>(vbuf + (4 * i + g) * kVPitch + 8 * lo) = vr[8 * c + i];
-      wave_lds_sync();
+      wave_lds_order();
 #pragma unroll
       for (int d = 0; d < 8; ++d) {
         const v4i16 r0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
@@ -792,13 +829,43 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
             (__attribute__((address_space(3))) v4i16*)(vbuf + (16 + 4 * g + rk) * kVPitch + 16 * d + 4 * cq));
         const bf16x8 b = __builtin_bit_cast(bf16x8, __builtin_shufflevector(r0, r1, 0, 1, 2, 3, 4, 5, 6, 7));
 #pragma unroll
-        for (int j = 0; j < 3; ++j) acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c][j], b, acc[d], 0, 0, 0);
+        for (int j = 0; j < NP; ++j) acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[c][j], b, acc[d], 0, 0, 0);
       }
-      wave_lds_sync();  // the reads of this half complete before the next half is written
+      wave_lds_order();  // the reads of this half come before the next half's writes
     }
   }
-  // acc[d][r]: head 4g + r, dim 16d + lo.  A block's first tile divides
-  // its sums by the mass l_h written to the record above; a later tile's
+  // acc[d][r]: row 4g + r of A, dim 16d + lo.  The parts' rows are added by
+  // swapping halves (then rows) of two accumulators and adding the pair,
+  // which leaves each lane the sums of fewer dims, all lanes at work: ND
+  // dims 16 (d + DG dg) + lo of heads HG hg + r.
+  constexpr int ND = G > 8 ? 8 : G > 4 ? 4 : 2;
+  f32x4 sum[ND];
+  if constexpr (G > 8) {
+#pragma unroll
+    for (int d = 0; d < ND; ++d) sum[d] = acc[d];
+  } else {
+#pragma unroll
+    for (int d = 0; d < 4; ++d)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const auto x = __builtin_amdgcn_permlane32_swap(__float_as_int(acc[d][r]), __float_as_int(acc[d + 4][r]), false, false);
+        acc[d][r] = __int_as_float(x[0]) + __int_as_float(x[1]);
+      }
+#pragma unroll
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        if constexpr (G > 4) {
+          sum[d][r] = acc[d][r];
+        } else {
+          const auto x = __builtin_amdgcn_permlane16_swap(__float_as_int(acc[d][r]), __float_as_int(acc[d + 2][r]), false, false);
+          sum[d][r] = __int_as_float(x[0]) + __int_as_float(x[1]);
+        }
+      }
+  }
+  const int h0 = G > 8 ? 4 * g : G > 4 ? 4 * (g & 1) : 0;                      // head of r = 0
+  float* const to = rec + h0 * kD + 16 * (G > 8 ? 0 : G > 4 ? 4 * (g >> 1) : 2 * g) + lo;  // its dim of d = 0
+  // A block's first tile divides its sums by the mass l_h; a later tile's
   // fold factors come from row 0 of the lanes (g = 0, head lo) through the
   // staging buffer, which the P.V loop no longer reads (a record never
   // stages its own later tiles: records stage only blocks of one tile).
@@ -807,13 +874,12 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
     const float inv_l = ls > 0.f ? fast_rcp(ls) : 0.f;
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int h = 4 * g + r;
-      if (h < G) {
+      if (r < G) {
         float inv = read_lane(inv_l, r);
-        if constexpr (G > 4) inv = g == 1 ? read_lane(inv_l, 4 + r) : inv;
-        if constexpr (G > 8) inv = g == 2 ? read_lane(inv_l, 8 + r) : g == 3 ? read_lane(inv_l, 12 + r) : inv;
+        if constexpr (G > 4) inv = h0 == 4 ? read_lane(inv_l, 4 + r) : inv;
+        if constexpr (G > 8) inv = h0 == 8 ? read_lane(inv_l, 8 + r) : h0 == 12 ? read_lane(inv_l, 12 + r) : inv;
 #pragma unroll
-        for (int d = 0; d < 8; ++d) rec[h * kD + 16 * d + lo] = __fmul_rn(acc[d][r], inv);
+        for (int d = 0; d < ND; ++d) to[r * kD + 16 * d] = __fmul_rn(sum[d][r], inv);
       }
     }
     return;
@@ -836,13 +902,12 @@ __device__ void compute_tile(const KernelParams& P, int kvh, int L, int tok0, co
   wave_lds_sync();
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
-    const int h = 4 * g + r;
-    if (h < G) {
-      const float so = scale[h], sn = scale[G + h];
+    if (r < G) {
+      const float so = scale[h0 + r], sn = scale[G + h0 + r];
 #pragma unroll
-      for (int d = 0; d < 8; ++d) {
-        float* x = rec + h * kD + 16 * d + lo;
-        *x = __fadd_rn(__fmul_rn(*x, so), __fmul_rn(acc[d][r], sn));
+      for (int d = 0; d < ND; ++d) {
+        float* x = to + r * kD + 16 * d;
+        *x = __fadd_rn(__fmul_rn(*x, so), __fmul_rn(sum[d][r], sn));
       }
     }
   }
@@ -864,11 +929,11 @@ __device__ __forceinline__ void step_block(State<G>& s, const Run<G>& run, const
 // ---- phase 2 helpers ----------------------------------------------------------
 // Chunk geometry: the first lead_chunks chunks of a traversal hold
 // lead_blocks blocks each, every later one chunk_blocks.
-__device__ __forceinline__ int chunk_start(const KernelParams& P, int k) {
+__device__ __forceinline__ int chunk_start(Params& P, int k) {
   return k < P.lead_chunks ? k * P.lead_blocks
                            : P.lead_chunks * P.lead_blocks + (k - P.lead_chunks) * P.chunk_blocks;
 }
-__device__ __forceinline__ int chunks_for(const KernelParams& P, int T) {
+__device__ __forceinline__ int chunks_for(Params& P, int T) {
   const int lead_T = P.lead_chunks * P.lead_blocks;
   return T <= lead_T ? (T + P.lead_blocks - 1) / P.lead_blocks
                      : P.lead_chunks + (T - lead_T + P.chunk_blocks - 1) / P.chunk_blocks;
@@ -925,14 +990,14 @@ __device__ __forceinline__ StabState stab_fold(StabState x, StabSummary y, int t
 __device__ __forceinline__ bool stop_word_before(uint64_t v, uint64_t epoch, int me) {
   return (v >> kQueueBits) == epoch && (int)(v & ((1ull << kQueueBits) - 1ull)) < me;
 }
-__device__ __forceinline__ bool stop_announced_before(const KernelParams& P, int gidx, int me) {
+__device__ __forceinline__ bool stop_announced_before(Params& P, int gidx, int me) {
   return stop_word_before(ld_relaxed(P.stop_word + gidx), P.epoch, me);
 }
 // Lowers the announcement to chunk k unless this call already announced a
 // chunk <= k (a word of an earlier call, whatever its bits, is replaced).
 // Several chunks of a group may announce; each compare-and-swap that fails
 // saw another announcement land, so the loop ends.  Lane 0 only.
-__device__ void announce_stop(const KernelParams& P, int gidx, int k) {
+__device__ void announce_stop(Params& P, int gidx, int k) {
   stress_delay(P, gidx, k, 8);
   uint64_t* w = P.stop_word + gidx;
   const uint64_t mine = (P.epoch << kQueueBits) | (uint64_t)k;
@@ -949,7 +1014,7 @@ __device__ void announce_stop(const KernelParams& P, int gidx, int k) {
 // -1 if all chunks 0..me-1 have state >= need_lo and none >= need_hi, or -2
 // when a stop in a chunk before `me` has been announced or the spin limit is
 // reached (the error word is set then).  Wave-uniform.
-__device__ int lookback_scan(const KernelParams& P, int gidx, int me, uint32_t need_lo,
+__device__ int lookback_scan(Params& P, int gidx, int me, uint32_t need_lo,
                              uint32_t need_hi, int lane) {
   const uint64_t* flags = P.flags + (int64_t)gidx * P.max_chunks;
   int hi = me - 1;
@@ -975,7 +1040,7 @@ __device__ int lookback_scan(const KernelParams& P, int gidx, int me, uint32_t n
 
 // One pass of lookback_scan with no wait: the index found, -1 for an empty
 // prefix, or -3 when a chunk in the way has not published yet.
-__device__ int lookback_once(const KernelParams& P, int gidx, int me, uint32_t need_lo,
+__device__ int lookback_once(Params& P, int gidx, int me, uint32_t need_lo,
                              uint32_t need_hi, int lane) {
   const uint64_t* flags = P.flags + (int64_t)gidx * P.max_chunks;
   for (int hi = me - 1; hi >= 0; hi -= 64) {
@@ -1019,7 +1084,7 @@ __device__ __forceinline__ StabSummary seg_combine(StabSummary a, StabSummary b,
 // state, which is the fold of every chunk up to it, so the summary already
 // used gives the same integers.  Returns false when a stop before `me` has
 // been announced or the spin limit is reached.
-__device__ bool stab_entering(const KernelParams& P, int gidx, int me, StabState& x, int lane) {
+__device__ bool stab_entering(Params& P, int gidx, int me, StabState& x, int lane) {
   const uint64_t* flags = P.flags + (int64_t)gidx * P.max_chunks;
   StabSummary acc{0, 0, 0, -1};  // composition of the chunks after the window
   int hi = me - 1, j = -1;       // j: the chunk that holds the state, if any
@@ -1082,7 +1147,7 @@ __device__ bool stab_entering(const KernelParams& P, int gidx, int me, StabState
 
 // States whose data sits in the workspace records: the flag goes out once
 // the record stores have completed.
-__device__ __forceinline__ void publish(const KernelParams& P, int gidx, int k, uint32_t state, int lane) {
+__device__ __forceinline__ void publish(Params& P, int gidx, int k, uint32_t state, int lane) {
   stress_delay(P, gidx, k, 1);
   stores_complete();
   if (lane == 0)
@@ -1090,7 +1155,7 @@ __device__ __forceinline__ void publish(const KernelParams& P, int gidx, int k, 
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // States carried in the flag word itself: one store, no wait.
-__device__ __forceinline__ void publish_word(const KernelParams& P, int gidx, int k, uint32_t state,
+__device__ __forceinline__ void publish_word(Params& P, int gidx, int k, uint32_t state,
                                              uint32_t payload, int lane) {
   stress_delay(P, gidx, k, 2 + (int)state);
   if (lane == 0)
@@ -1098,7 +1163,7 @@ __device__ __forceinline__ void publish_word(const KernelParams& P, int gidx, in
                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 template <int G>
-__device__ void write_outputs(const KernelParams& P, int b, int kvh, const State<G>& s,
+__device__ void write_outputs(Params& P, int b, int kvh, const State<G>& s,
                               int stop, int lane, uint32_t heads = 0xffffffffu,
                               bool write_stop = true) {
   const int c = lane & 15, r = lane >> 4;
@@ -1135,7 +1200,7 @@ struct GroupInfo {
 // a kernel read outside the arrays the shape describes).
 // From the raw sequence length and list length of the group (the list
 // length is ignored for dense traversals).
-__device__ __forceinline__ GroupInfo group_info_raw(const KernelParams& P, int gidx, int L_raw, int T_raw) {
+__device__ __forceinline__ GroupInfo group_info_raw(Params& P, int gidx, int L_raw, int T_raw) {
   GroupInfo g;
   g.b = gidx / P.num_kv_heads;
   g.kvh = gidx - g.b * P.num_kv_heads;
@@ -1156,18 +1221,18 @@ __device__ __forceinline__ GroupInfo group_info_raw(const KernelParams& P, int g
   return g;
 }
 
-__device__ __forceinline__ int raw_list_len(const KernelParams& P, int gidx) {
+__device__ __forceinline__ int raw_list_len(Params& P, int gidx) {
   if (!P.block_list) return 0;
   const int b = gidx / P.num_kv_heads;
   return P.block_list_len[P.list_per_head ? gidx : b];
 }
 
-__device__ __forceinline__ GroupInfo group_info(const KernelParams& P, int gidx) {
+__device__ __forceinline__ GroupInfo group_info(Params& P, int gidx) {
   return group_info_raw(P, gidx, P.seq_lens[gidx / P.num_kv_heads], raw_list_len(P, gidx));
 }
 
 template <int G>
-__device__ void write_empty_wave(const KernelParams& P, int b, int kvh, int lane) {
+__device__ void write_empty_wave(Params& P, int b, int kvh, int lane) {
   for (int i = lane; i < G * kD; i += 64) {
     const int64_t idx = ((int64_t)b * P.num_q_heads + kvh * G) * kD + i;
     if (P.out_bf16) static_cast<uint16_t*>(P.out)[idx] = 0;
@@ -1182,7 +1247,7 @@ __device__ void write_empty_wave(const KernelParams& P, int b, int kvh, int lane
 }
 
 constexpr int kLoaders = kWaves - 1;   // wavefronts 1..3 stream tiles
-constexpr int kMaxSlots = 3;           // chunk buffers in LDS (the plan picks 2 or 3)
+constexpr int kSlots = kChunkSlots;    // chunk buffers in LDS
 constexpr int kLenCache = 256;         // sequence lengths kept in LDS
 enum SlotState : int { kSlotFree = 0, kSlotLoading = 1, kSlotReady = 2, kSlotEnd = 3 };
 // slot metadata words
@@ -1211,16 +1276,16 @@ __device__ __forceinline__ void lds_st(int* p, int v) {
 // same list, and each list is handed out in increasing order: a chunk only
 // ever waits on chunks that some workgroup already holds.  Lane 0 only /
 // wave-uniform result.
-__device__ __forceinline__ uint64_t* queue_word(const KernelParams& P, int x) {
+__device__ __forceinline__ uint64_t* queue_word(Params& P, int x) {
   return P.queue + (int64_t)x * kQueueStride;
 }
 
-__device__ __forceinline__ uint64_t claim_issue(const KernelParams& P, int x, int lane) {
+__device__ __forceinline__ uint64_t claim_issue(Params& P, int x, int lane) {
   return lane == 0 ? __hip_atomic_fetch_add(queue_word(P, x), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                    : 0ull;
 }
 
-__device__ int claim_finish(const KernelParams& P, int x, uint64_t v, int lane) {
+__device__ int claim_finish(Params& P, int x, uint64_t v, int lane) {
   int q = 0;
   if (lane == 0) {
     uint64_t* w = queue_word(P, x);
@@ -1264,14 +1329,14 @@ __device__ int claim_finish(const KernelParams& P, int x, uint64_t v, int lane) 
 // written by lane h for head h and published by the chunk's flag as in the
 // group reading.  A summary stays valid after the chunk's state is
 // published, so the fold below never meets a changed word.
-__device__ __forceinline__ int32_t* head_area(const KernelParams& P, int gidx, int k, int G) {
+__device__ __forceinline__ int32_t* head_area(Params& P, int gidx, int k, int G) {
   return P.head_area + ((int64_t)gidx * P.max_chunks + k) * (int64_t)(G * 8);
 }
 
 // The nearest chunk before `me` that published its stability state, such
 // that every chunk between published its summary: j >= -1, or -2 when a
 // stop before `me` has been announced or a wait gave up.
-__device__ int stab_scan(const KernelParams& P, int gidx, int me, int lane) {
+__device__ int stab_scan(Params& P, int gidx, int me, int lane) {
   const uint64_t* flags = P.flags + (int64_t)gidx * P.max_chunks;
   int hi = me - 1;
   uint32_t it = 0;
@@ -1295,7 +1360,7 @@ __device__ int stab_scan(const KernelParams& P, int gidx, int me, int lane) {
 }
 
 template <int G>
-__device__ void resolve_heads(const KernelParams& P, int gidx, int k, const GroupInfo& gi,
+__device__ void resolve_heads(Params& P, int gidx, int k, const GroupInfo& gi,
                               const float* blocks, const State<G>& pre, const Run<G>& run,
                               uint32_t head_bits, int t0, int nb, int lane) {
   constexpr int REC = Cfg<G>::REC;
@@ -1437,7 +1502,7 @@ __device__ void resolve_heads(const KernelParams& P, int gidx, int k, const Grou
 // Phase 2 for one chunk (resolver wavefront).  `blocks` holds the chunk's
 // block records.
 template <int G, bool PH>
-__device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const GroupInfo& gi,
+__device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
                               const float* blocks, int lane) {
   constexpr int REC = Cfg<G>::REC;
   const int b = gi.b, kvh = gi.kvh, T = gi.T, n_chunks = gi.n_chunks;
@@ -1727,36 +1792,31 @@ __device__ void resolve_chunk(const KernelParams& P, int gidx, int k, const Grou
 // only once a buffer is free, and every wait targets a chunk claimed
 // earlier, so the launch always makes progress.
 template <int G, bool PH, bool WIDE>
-// (groups of 16 heads need the bound to keep two workgroups per CU; for
-// the smaller groups the compiler's own choice was faster)
-__global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelParams P) {
+__global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelParams) {
+  Params* const args = (Params*)__builtin_amdgcn_kernarg_segment_ptr();
   // the dynamic buffers must start 16-byte aligned (128-bit LDS accesses):
   // the static block below is a multiple of 16 bytes
   extern __shared__ __align__(16) float smem[];
-  __shared__ __align__(16) int s_meta[kMaxSlots][8];
+  __shared__ __align__(16) int s_meta[kSlots][8];
   // lengths of the first kLenCache sequences: a dense traversal's claims
   // need no round trip
   __shared__ __align__(16) int s_len[kLenCache];
-  static_assert(sizeof(int) * (kMaxSlots * 8 + kLenCache) % 16 == 0,
+  static_assert(sizeof(int) * (kSlots * 8 + kLenCache) % 16 == 0,
                 "static LDS must keep the dynamic part aligned");
   constexpr int REC = Cfg<G>::REC;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  const int n_groups = P.batch * P.num_kv_heads;
-  const int CT = P.chunk_recs_lds;
-  const int slot_floats = CT * REC;
-  const int n_slots = P.n_slots;
-  // V staging buffers of the loaders after the chunk buffers (16-byte aligned)
-  uint16_t* vbuf_all = reinterpret_cast<uint16_t*>(smem + ((n_slots * slot_floats + 3) & ~3));
+  const int slot_floats = args->chunk_blocks * REC;
 
-  if (tid < kMaxSlots * 8) (&s_meta[0][0])[tid] = (tid % 8 == kMetaSeq) ? -1 : 0;
-  for (int i = tid; i < min(P.batch, kLenCache); i += kThreads) s_len[i] = P.seq_lens[i];
+  if (tid < kSlots * 8) (&s_meta[0][0])[tid] = (tid % 8 == kMetaSeq) ? -1 : 0;
+  for (int i = tid; i < min(args->batch, kLenCache); i += kThreads) s_len[i] = args->seq_lens[i];
   __syncthreads();
 
   if (wave == 0) {
     // ---------------- resolver ----------------
     __builtin_amdgcn_s_setprio(3);
     for (int it = 0;; ++it) {
-      const int slot = it % n_slots;
+      Params& P = *fresh(args);
+      const int slot = it % kSlots;
       int st = kSlotFree;
       for (uint32_t spin = 0;; ++spin) {
         st = lds_ld(&s_meta[slot][kMetaState]);
@@ -1771,7 +1831,7 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
         float* base = smem + slot * slot_floats;
         const GroupInfo gi = group_info_raw(P, gidx, lds_uniform(&s_meta[slot][kMetaLen]),
                                             lds_uniform(&s_meta[slot][kMetaListLen]));
-        resolve_chunk<G, PH>(P, gidx, k, gi, base, lane);
+        resolve_chunk<G, PH>(*fresh(args), gidx, k, gi, base, lane);
       }
       wave_lds_sync();
       if (lane == 0) lds_st(&s_meta[slot][kMetaState], kSlotFree);
@@ -1780,9 +1840,11 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
 
   // ---------------- loaders ----------------
   const int lw = wave - 1;
-  // (a loader's own staging buffer: a half tile, or a quarter tile for 8 or
-  // more heads; unused when V is staged in the records)
-  uint16_t* vbuf = vbuf_all + lw * (G >= 8 ? 16 * kVRow : kVBufU16);
+  // (a loader's own staging buffer after the chunk buffers, 16-byte aligned:
+  // a half tile, or a quarter tile for 8 or more heads; unused when V is
+  // staged in the records)
+  uint16_t* vbuf = reinterpret_cast<uint16_t*>(smem + ((kSlots * slot_floats + 3) & ~3)) +
+                   lw * (G >= 8 ? 16 * kVRow : kVBufU16);
   // leader: the queue it claims from (its own first, then the others in
   // turn once its own is used up) and the queues found used up
   int qx = blockIdx.x % kQueues;
@@ -1790,7 +1852,8 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
   constexpr uint64_t kAllUsedUp = kQueues >= 64 ? ~0ull : ((1ull << kQueues) - 1ull);
 
   for (int it = 0;; ++it) {
-    const int slot = it % n_slots;
+    Params& P = *fresh(args);
+    const int slot = it % kSlots;
     if (lw == 0) {
       // leader: wait for the buffer, then claim the next chunk of the list
       bool gave_up = false;
@@ -1801,6 +1864,7 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
         }
         __builtin_amdgcn_s_sleep(1);
       }
+      const int n_groups = P.batch * P.num_kv_heads;
       int gsel = -1, ksel = -1, len_sel = 0, list_sel = 0;
       while (!gave_up && used_up != kAllUsedUp) {
         const int nx = (n_groups - qx + kQueues - 1) / kQueues;  // groups in queue qx
@@ -1927,7 +1991,7 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
         const int tok0 = __builtin_amdgcn_readlane(my_tok0, 4 * m);
         const int pg[4] = {__builtin_amdgcn_readlane(my_page, 4 * m), __builtin_amdgcn_readlane(my_page, 4 * m + 1),
                            __builtin_amdgcn_readlane(my_page, 4 * m + 2), __builtin_amdgcn_readlane(my_page, 4 * m + 3)};
-        compute_tile<G, WIDE>(P, gi.kvh, gi.L, tok0, pg, qa,
+        compute_tile<G, WIDE>(*fresh(args), gi.kvh, gi.L, tok0, pg, qa,
                         P.v_in_record ? reinterpret_cast<uint16_t*>(blocks + i * REC) : vbuf,
                         blocks + i * REC, j > 0);
         if (stop_word_before(sw, P.epoch, k)) {
@@ -1978,7 +2042,7 @@ int launch_w(const Plan& plan, const KernelParams& params, hipStream_t stream) {
   // A function of the shape and the device only; the results are the same
   // bits either way.
   KernelParams p = params;
-  p.look_first = grid * plan.slots <= (int64_t)8 * plan.n_groups ? 1 : 0;
+  p.look_first = grid * kChunkSlots <= (int64_t)8 * plan.n_groups ? 1 : 0;
   auto kernel = art_decode_kernel<G, PH, WIDE>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kThreads),
                      plan.lds_bytes, stream, p);
