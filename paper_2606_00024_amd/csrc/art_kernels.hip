@@ -1269,9 +1269,15 @@ __device__ __forceinline__ void lds_st(int* p, int v) {
 // (see the claim).  Each
 // list is handed out from its own workspace word (call epoch << 24 | next
 // index) by one fetch-and-add (claim_issue; claim_finish decodes it), so
-// that claims spread over kQueues atomic units.  A word left by an earlier
-// call is replaced by compare-and-swap with this call's epoch and index 1,
-// which hands out index 0; claims that raced with the replacement retry.
+// that claims spread over kQueues atomic units.  A workgroup's first claim
+// from a queue sends an atomic maximum with this call's epoch and index 0
+// ahead of its fetch-and-add (the two reach the word in order), so that a
+// word left by an earlier call starts over with no round trip of its own:
+// replacing it by compare-and-swap took three dependent round trips with
+// every workgroup of the queue on one word (2.5 to 4.4 us of each launch's
+// start).  Only a word whose epoch is higher (the workspace last served
+// another copy of the library, whose call counter is its own) is replaced
+// that way; claims that raced with the replacement retry.
 // Every chunk a chunk can wait on belongs to the same group, hence to the
 // same list, and each list is handed out in increasing order: a chunk only
 // ever waits on chunks that some workgroup already holds.  Lane 0 only /
@@ -1280,7 +1286,9 @@ __device__ __forceinline__ uint64_t* queue_word(Params& P, int x) {
   return P.queue + (int64_t)x * kQueueStride;
 }
 
-__device__ __forceinline__ uint64_t claim_issue(Params& P, int x, int lane) {
+__device__ __forceinline__ uint64_t claim_issue(Params& P, int x, bool first, int lane) {
+  if (first && lane == 0)
+    __hip_atomic_fetch_max(queue_word(P, x), P.epoch << kQueueBits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   return lane == 0 ? __hip_atomic_fetch_add(queue_word(P, x), 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
                    : 0ull;
 }
@@ -1845,11 +1853,15 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
   // staged in the records)
   uint16_t* vbuf = reinterpret_cast<uint16_t*>(smem + ((kSlots * slot_floats + 3) & ~3)) +
                    lw * (G >= 8 ? 16 * kVRow : kVBufU16);
-  // leader: the queue it claims from (its own first, then the others in
-  // turn once its own is used up) and the queues found used up
-  int qx = blockIdx.x % kQueues;
-  uint64_t used_up = 0;
-  constexpr uint64_t kAllUsedUp = kQueues >= 64 ? ~0ull : ((1ull << kQueues) - 1ull);
+  // leader: the queue it claims from (its own first, then the others in turn
+  // once its own is used up), the queues that may still hold work (those past
+  // the number of groups never do: with two groups, six of eight workgroups
+  // spent their first claims on them) and those it has claimed from.  (The
+  // first claim issued before the lengths are read, to overlap the two round
+  // trips, was no faster on the listed shapes and 2 % slower on others.)
+  const int n_queues = min(kQueues, args->batch * args->num_kv_heads);
+  int qx = (int)(blockIdx.x % (unsigned)n_queues);
+  uint32_t open = (1u << n_queues) - 1u, entered = 0;
 
   for (int it = 0;; ++it) {
     Params& P = *fresh(args);
@@ -1866,12 +1878,21 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
       }
       const int n_groups = P.batch * P.num_kv_heads;
       int gsel = -1, ksel = -1, len_sel = 0, list_sel = 0;
-      while (!gave_up && used_up != kAllUsedUp) {
+      while (!gave_up && open) {
         const int nx = (n_groups - qx + kQueues - 1) / kQueues;  // groups in queue qx
-        const int i = claim_finish(P, qx, claim_issue(P, qx, lane), lane);
+        const uint64_t claim = claim_issue(P, qx, !((entered >> qx) & 1u), lane);
+        entered |= 1u << qx;
+        const int i = claim_finish(P, qx, claim, lane);
         if (i >= nx * P.work_chunks) {
-          used_up |= 1ull << qx;
-          qx = (qx + 1) % kQueues;
+          // this queue is used up: go on with the next one.  (Looking at
+          // all their words first, to pass over those that are used up as
+          // well, cost 7-9 % on launches of many groups: the reads meet the
+          // other workgroups' claims on the same lines.)
+          open &= ~(1u << qx);
+          if (open) {
+            const uint32_t after = open & ~((2u << qx) - 1u);
+            qx = __builtin_ctz(after ? after : open);
+          }
           continue;
         }
         int g = qx + kQueues * (i % nx);
