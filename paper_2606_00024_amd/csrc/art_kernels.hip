@@ -294,6 +294,7 @@ struct Cfg {
   static constexpr int REC = G * kD + 2 * G;        // floats per LDS tile record
   static constexpr int REP = G > 8 ? 1 : G > 4 ? 2 : 4;  // copies of the heads over the 16 score columns
   static constexpr int COLS = 16 / REP;             // columns of one copy
+  static constexpr int GANG = G > 8 ? 1 : 3;        // blocks the resolver takes at a time (the loads of all in flight)
 };
 
 // Per-head softmax state in the "state layout": lane l covers dims
@@ -451,16 +452,18 @@ __device__ __forceinline__ void aggregate(State<G>& s, const float* blocks, int 
 #pragma unroll
     for (int e = 0; e < 8; ++e) s.o[k][e] = 0.f;
   }
-#pragma unroll 2
-  for (int i = 0; i < nb; ++i) {
+  // (blocks past nb read the last one's record with weight 0)
+  for (int i0 = 0; i0 < nb; i0 += Cfg<G>::GANG) {
 #pragma unroll
-    for (int k = 0; k < HPL; ++k) {
-      float p[8];
-      read_output<G>(blocks + i * Cfg<G>::REC, k, lane, p);
-      const float wi = row_lane(w[k], i, lane);
+    for (int u = 0; u < Cfg<G>::GANG; ++u)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) s.o[k][e] = __builtin_fmaf(wi, p[e], s.o[k][e]);
-    }
+      for (int k = 0; k < HPL; ++k) {
+        float p[8];
+        read_output<G>(blocks + min(i0 + u, nb - 1) * Cfg<G>::REC, k, lane, p);
+        const float wi = row_lane(w[k], i0 + u, lane);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s.o[k][e] = __builtin_fmaf(wi, p[e], s.o[k][e]);
+      }
   }
 }
 
@@ -1536,7 +1539,7 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
   // timing.  No chunk follows the last one, so it publishes neither its
   // aggregate nor its inclusive state.
   constexpr int HPL = Cfg<G>::HPL;
-  constexpr int FW = 8 / HPL > 0 ? 8 / HPL : 1;
+  constexpr int FW = 12 / HPL;   // (12 in place of 8: one sequence of 32K tokens 50.4 -> 48.5 us; 16 no better)
   int j;
   if (k == 0) {
     j = -1;
@@ -1629,7 +1632,8 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
   // Replay the chunk's blocks from the prefix with the stability test.  The
   // steps run in order (each needs the state after the previous block); the
   // row sums of |d|^2 and o(t-1).d of block i stay in lane c = i of the
-  // head's row with |o(t-1)|^2, and |o(t)|^2 follows as
+  // head's row with |o(t-1)|^2 (blocks past the chunk's last add nothing and
+  // are masked out below), and |o(t)|^2 follows as
   // |o(t-1)|^2 + 2 o(t-1).d + |d|^2.  The verdicts of all blocks and heads
   // are then taken at once, lane (r, c) for block c of head r + 4k.  (One
   // verdict after the other and merges with their exponentials inside took
@@ -1663,53 +1667,56 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
       n_prev[kk] = row_sum(n0);
       q0[kk] = q1[kk] = qdd[kk] = qod[kk] = acc_dx[kk] = 0.f;
     }
-    for (int i = 0; i < nb; ++i) {
+    // step i of slot kk; the sums it leaves in lane c = i
+    auto step = [&](int i, int kk, bool plain) {
+      float p[8], d[8], o0[8];
+      read_output<G>(blocks + min(i, nb - 1) * REC, kk, lane, p);
+      const float L0 = s.L[kk];
 #pragma unroll
-      for (int kk = 0; kk < HPL; ++kk) {
-        float p[8], d[8], o0[8];
-        read_output<G>(blocks + i * REC, kk, lane, p);
-        const float L0 = s.L[kk];
+      for (int e = 0; e < 8; ++e) o0[e] = s.o[kk][e];
+      run_step<G>(s, run, kk, i, lane, p, d);
+      float dd = 0.f, od = 0.f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) o0[e] = s.o[kk][e];
-        run_step<G>(s, run, kk, i, lane, p, d);
-        float dd = 0.f, od = 0.f;
-        if (full_probe) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            dd = __builtin_fmaf(d[e], d[e], dd);
-            od = __builtin_fmaf(o0[e], d[e], od);
-          }
-        } else {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            dd = __builtin_fmaf(d[e] * pw[e], d[e], dd);
-            od = __builtin_fmaf(o0[e] * pw[e], d[e], od);
-          }
-        }
-        dd = row_sum(dd);
-        od = row_sum(od);
-        const float n0 = n_prev[kk], n1 = __fadd_rn(__fadd_rn(n0, __fmul_rn(2.f, od)), dd);   // |x(t)|^2
-        n_prev[kk] = n1;
-        if (c == i) {
-          q0[kk] = n0;
-          q1[kk] = n1;
-          qdd[kk] = dd;
-          qod[kk] = od;
-        }
-        if (on_acc) {
-          // change of the unnormalised accumulator L o, each side in its
-          // own max reference (L is the mass relative to the running max):
-          // it takes the place of |d|^2 in the magnitude test below
-          float dx2 = 0.f;
-#pragma unroll
-          for (int e = 0; e < 8; ++e) {
-            const float dx = __fsub_rn(__fmul_rn(s.L[kk], s.o[kk][e]), __fmul_rn(L0, o0[e]));
-            dx2 = __builtin_fmaf(dx * pw[e], dx, dx2);
-          }
-          dx2 = row_sum(dx2);
-          if (c == i) acc_dx[kk] = dx2;
-        }
+      for (int e = 0; e < 8; ++e) {
+        dd = __builtin_fmaf(plain ? d[e] : d[e] * pw[e], d[e], dd);
+        od = __builtin_fmaf(plain ? o0[e] : o0[e] * pw[e], d[e], od);
       }
+      dd = row_sum(dd);
+      od = row_sum(od);
+      const float n0 = n_prev[kk], n1 = __fadd_rn(__fadd_rn(n0, __fmul_rn(2.f, od)), dd);   // |x(t)|^2
+      n_prev[kk] = n1;
+      if (c == i) {
+        q0[kk] = n0;
+        q1[kk] = n1;
+        qdd[kk] = dd;
+        qod[kk] = od;
+      }
+      if (plain) return;
+      // change of the unnormalised accumulator L o, each side in its own max
+      // reference (L is the mass relative to the running max): on request it
+      // takes the place of |d|^2 in the magnitude test below
+      float dx2 = 0.f;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float dx = __fsub_rn(__fmul_rn(s.L[kk], s.o[kk][e]), __fmul_rn(L0, o0[e]));
+        dx2 = __builtin_fmaf(dx * pw[e], dx, dx2);
+      }
+      dx2 = row_sum(dx2);
+      if (c == i) acc_dx[kk] = dx2;
+    };
+    if (full_probe && !on_acc) {
+      // (no branch between the steps of a gang: their loads, weights and row
+      // sums overlap)
+      for (int i0 = 0; i0 < nb; i0 += Cfg<G>::GANG)
+#pragma unroll
+        for (int u = 0; u < Cfg<G>::GANG; ++u)
+#pragma unroll
+          for (int kk = 0; kk < HPL; ++kk) step(i0 + u, kk, true);
+    } else {
+#pragma unroll 1
+      for (int i = 0; i < nb; ++i)
+#pragma unroll
+        for (int kk = 0; kk < HPL; ++kk) step(i, kk, false);
     }
 #pragma unroll
     for (int kk = 0; kk < HPL; ++kk) s.m[kk] = row_lane(run.m[kk], 15, lane);
