@@ -98,8 +98,9 @@ typedef struct {
  * removes that half of the test (the ablations of Table 3).  patience >= 1;
  * patience = 1 is "no patience"; INT32_MAX runs the detector without ever
  * stopping.  chunk_blocks = 0 lets the library pick the split of each
- * traversal into chunks from the shape alone (never from the data or the
- * thresholds: four leading chunks of 3 blocks, then chunks of up to 9);
+ * traversal into chunks from the shape, the order and no_detector alone
+ * (never from the data or the thresholds: with the test, short leading chunks
+ * of 3 blocks, then chunks of up to 9; without it, chunks of up to 12);
  * 1..16 asks for that many blocks in every chunk (capped at what the
  * shared-memory budget holds for the shape).  The chunking changes
  * rounding only.

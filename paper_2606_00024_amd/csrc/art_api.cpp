@@ -41,6 +41,7 @@ uint64_t next_epoch() {
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
 constexpr int kLeadChunks = 4;  // leading short chunks per traversal
+constexpr int kLeadChunksEarly = 16;
 constexpr int kLeadBlocks = 3;  // blocks in each of them
 
 // Chunks of a traversal of T blocks (the kernel's chunks_for).
@@ -90,11 +91,11 @@ art_status check_shape(const art_decode_shape* s, const art_decode_opts* o) {
     return ART_OK;
 }
 
-// Everything about the launch is decided here from the shape (and the
-// chunk_blocks option): never from the data or the thresholds.
-art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* p) {
-    art_status st = check_shape(s, o);
-    if (st != ART_OK) return st;
+// Everything about the launch is decided here from the shape and the options
+// (chunk_blocks, the order, whether the test runs): never from the data or
+// the thresholds.  `compact` keeps to the longest chunks and the fewest
+// leading ones (see make_plan).
+art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool compact, Plan* p) {
     const int g = s->num_q_heads / s->num_kv_heads;
     const int tpb = s->block_size / art::kTile;
     const int64_t cap_tokens = (int64_t)s->max_pages_per_seq * s->page_size;
@@ -123,19 +124,28 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     while (c_max > 1 && (c_max + 2) / 3 * tpb > art::kMaxChunkTiles) --c_max;
     if (c_max < 1) return ART_ERR_UNSUPPORTED;
 
+    // walks that tend to stop early: lists (best blocks first) and oldest-first
+    // walks (the sinks first) of groups of few heads
+    const bool early = !compact && !o->no_detector && g <= 4 &&
+                       (s->max_blocks_per_list > 0 || o->dense_order == ART_ORDER_FORWARD);
     int C;
     if (o->chunk_blocks > 0) {
         C = o->chunk_blocks;
     } else {
-        // up to 9 blocks per chunk, a multiple of the three loaders when the
-        // budget allows; 6, then 3, only when the whole problem has fewer
-        // than 64 chunks.  (Measured: halving the chunk whenever there were
-        // fewer chunks than 1024 cost 17-210 % on problems of 2 to 16
-        // groups; the per-chunk work of the resolver outweighs the wider
-        // spread.)
-        C = c_max < 9 ? c_max : 9;
+        // up to 9 blocks per chunk (12 without the test, which has nothing
+        // to decide sooner), a multiple of the three loaders when the
+        // budget allows; less when the whole problem has fewer than 64
+        // chunks, or when five chunks would cover the traversal (16 ragged
+        // sequences of up to 32 blocks, g = 4: 34.6 us with chunks of 9, 31.5
+        // with 6).  Without the test, 12 in place of 9 took 8 x 32K tokens
+        // from 212.8 to 205.0 us and 1 x 128K from 132 to 126.  (Halving the
+        // chunk whenever there were fewer chunks than 1024 cost 17-210 % on
+        // problems of 2 to 16 groups; the per-chunk work of the resolver
+        // outweighs the wider spread.)
+        const int most = o->no_detector ? 12 : 9;
+        C = c_max < most ? c_max : most;
         if (C >= 3) C -= C % 3;
-        while (C > 3 && n_groups * ((t_cap + C - 1) / C) < 64) C -= 3;
+        while (C > 3 && (n_groups * ((t_cap + C - 1) / C) < 64 || (!compact && 5 * C > t_cap))) C -= 3;
         // the work list must fit a queue word
         while (C < c_max && n_groups * ((t_cap + C - 1) / C) + art::kQueueSlack >= (1 << art::kQueueBits)) C *= 2;
     }
@@ -143,12 +153,23 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     if (C < 1) C = 1;
     // Leading chunks of kLeadBlocks blocks: the first decisions of every
     // group come sooner, so that groups that stop early claim less past
-    // their stop (only with the default chunk size).
+    // their stop (only with the default chunk size).  Walks that tend to
+    // stop early have more of them: on 25 % lists of 128K caches 49.5 us with
+    // 16, 54 with 8, 56.5 with 4; oldest-first walks of 16K, 33 / 39 / 40; a
+    // recency-first batch of 8 x 32K, which stops later, 132 / 130 / 128.
+    // Without the test there is nothing to decide.
     int lead_chunks = 0, lead_blocks = C;
-    if (o->chunk_blocks == 0 && C > kLeadBlocks) {
-        lead_chunks = kLeadChunks;
+    if (o->chunk_blocks == 0 && C > kLeadBlocks && !o->no_detector) {
+        lead_chunks = early ? kLeadChunksEarly : kLeadChunks;
         lead_blocks = kLeadBlocks;
     }
+    // Workgroups per group, at most (never fewer than one per CU): beyond
+    // that, a few long traversals gain nothing but reads past their stops.
+    // Groups of up to 4 heads stop soonest: with 8 in place of 32, 32 such
+    // groups take 56 us in place of 75 on the 25 % lists and 39 in place of 52
+    // oldest-first, 87 in place of 92 recency-first at 4 x 32K tokens; if none
+    // of those stops, 125 in place of 118.
+    p->group_workgroups = o->no_detector || g > 4 ? 32 : 8;
     p->lead_chunks = lead_chunks;
     p->lead_blocks = lead_blocks;
     const int64_t max_chunks = chunks_for(t_cap, C, lead_chunks, lead_blocks);
@@ -177,6 +198,24 @@ art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* 
     if ((int64_t)max_chunks * 2 * p->record_floats * 4 > INT32_MAX) return ART_ERR_UNSUPPORTED;
     w.total = off;
     return ART_OK;
+}
+
+// The plan of a call.  Short leading chunks and short chunks cost workspace:
+// where only they would take a shape past the library's own scratch, or past
+// what the queue words and record offsets hold, it keeps the compact plan.
+art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* p) {
+    art_status st = check_shape(s, o);
+    if (st != ART_OK) return st;
+    st = plan_chunks(s, o, false, p);
+    if (st != ART_OK || p->ws.total > ART_STATIC_SCRATCH_BYTES) {
+        Plan compact;
+        const art_status sc = plan_chunks(s, o, true, &compact);
+        if (sc == ART_OK && (st != ART_OK || compact.ws.total <= ART_STATIC_SCRATCH_BYTES)) {
+            *p = compact;
+            st = sc;
+        }
+    }
+    return st;
 }
 
 // Host checks of a decode call and its plan (everything but the workspace).

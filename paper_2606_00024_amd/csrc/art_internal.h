@@ -61,6 +61,7 @@ struct Plan {
     int32_t t_cap;           // traversal length bound per group
     int32_t record_floats;   // floats per aggregate / inclusive record
     int32_t v_in_record;     // see KernelParams
+    int32_t group_workgroups; // workgroups a launch has per group, at most (and one per CU)
     size_t lds_bytes;        // dynamic LDS per workgroup
     WorkspaceLayout ws;
 };

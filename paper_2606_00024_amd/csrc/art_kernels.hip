@@ -2058,10 +2058,9 @@ int launch_w(const Plan& plan, const KernelParams& params, hipStream_t stream) {
     e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, art_decode_kernel<G, PH, WIDE>, kThreads, plan.lds_bytes);
   if (e != hipSuccess) return (int)e;
   if (per_cu < 1) per_cu = 1;
-  // As many workgroups as the chip holds, but at most 32 per group (and
-  // never fewer than one per CU): beyond that, a few long traversals gain
-  // nothing but reads past their stops.
-  const int64_t per_groups = max((int64_t)cus, (int64_t)32 * plan.n_groups);
+  // As many workgroups as the chip holds, but no more than the plan allows
+  // per group (and never fewer than one per CU).
+  const int64_t per_groups = max((int64_t)cus, (int64_t)plan.group_workgroups * plan.n_groups);
   const int64_t grid = min(work, min((int64_t)cus * per_cu, per_groups));
   // Chunks of one group in flight at once: about the launch's chunk buffers
   // over the groups.  Up to 8 (many groups), a chunk of a group of 8 or
