@@ -27,6 +27,9 @@ constexpr int64_t kQueueSlack = 1 << 16;
 // groups spread over all of them), each in its own 256-byte line.
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 32;  // uint64 words between queue words
+// The word of the queues found used up, this many uint64 words after the
+// error word (the 256 bytes that start with it hold nothing else).
+constexpr int kUsedUpWord = 16;
 
 // Progress of one chunk, published in bits 20..22 of its flag word (the
 // call's epoch is in bits 24..63, bits 0..19 carry the stability summary or

@@ -1329,6 +1329,49 @@ __device__ int claim_finish(Params& P, int x, uint64_t v, int lane) {
   return __builtin_amdgcn_readfirstlane(q);
 }
 
+// The queues used up so far: epoch << 24 | a bit per queue, in one word that
+// no claim touches.  The first claim past a queue's end sets its bit (one
+// writer per queue: with every such claim setting it, the word's atomics
+// alone took 20 us of a launch), and every claim reads the word along with
+// its own atomic, so that a workgroup whose queue is used up passes over the
+// others that are, instead of asking each in turn, an atomic and a round
+// trip each (the last 5 to 8 us of small launches).  A word of a higher epoch
+// (another copy of the library) is never taken for this call's.
+__device__ __forceinline__ uint64_t* used_up_word(Params& P) { return P.error_word + kUsedUpWord; }
+__device__ __forceinline__ void mark_used_up(Params& P, int x, int lane) {
+  if (lane == 0) {
+    __hip_atomic_fetch_max(used_up_word(P), P.epoch << kQueueBits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_fetch_or(used_up_word(P), 1ull << x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+}
+__device__ __forceinline__ uint32_t used_up_queues(Params& P, uint64_t word) {
+  return (word >> kQueueBits) == P.epoch ? __builtin_amdgcn_readfirstlane((uint32_t)word & ((1u << kQueues) - 1u)) : 0u;
+}
+
+// Group u of queue x: x + kQueues u, where within every full run of kQueues
+// groups the queues rotate by the run's index, so that each list mixes KV
+// heads instead of holding one head's groups of every sequence (whose stops
+// can fall close together and leave one list's workgroups with the late
+// work).  A bijection: every group belongs to one list.
+__device__ __forceinline__ int queue_group(int x, int u, int n_groups) {
+  const int g = x + kQueues * u;
+  return u < n_groups / kQueues ? kQueues * u + (x + u) % kQueues : g;
+}
+
+// How many chunks of group u of queue x (lane u, the first 64 groups) are
+// still of use: up to the announced stop, or all of its own (at least the
+// one that writes an empty traversal's outputs).  Later reads only lower it.
+__device__ __forceinline__ int live_chunks(Params& P, const int* s_len, int x, int nx, int n_groups, int lane) {
+  int live = 0;
+  if (lane < nx) {
+    const int g = queue_group(x, lane, n_groups), b = g / P.num_kv_heads;
+    const uint64_t sw = P.no_detector ? 0ull : ld_relaxed(P.stop_word + g);
+    live = max(group_info_raw(P, g, b < kLenCache ? s_len[b] : P.seq_lens[b], raw_list_len(P, g)).n_chunks, 1);
+    if ((sw >> kQueueBits) == P.epoch) live = min(live, (int)(sw & ((1ull << kQueueBits) - 1ull)) + 1);
+  }
+  return live;
+}
+
 // ---- per-query-head termination ---------------------------------------------
 // The per-head reading of the test: every query head of a group keeps its
 // own patience counter (Eq. 3) and stops on its own; its out and lse are
@@ -1860,18 +1903,28 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
   // staged in the records)
   uint16_t* vbuf = reinterpret_cast<uint16_t*>(smem + ((kSlots * slot_floats + 3) & ~3)) +
                    lw * (G >= 8 ? 16 * kVRow : kVBufU16);
-  // leader: the queue it claims from (its own first, then the others in turn
-  // once its own is used up), the queues that may still hold work (those past
+  // leader: the queue it claims from (its own first, as many workgroups to
+  // each as it has groups, then the others in turn once its own is used up),
+  // the queues that may still hold work (those past
   // the number of groups never do: with two groups, six of eight workgroups
   // spent their first claims on them) and those it has claimed from.  (The
   // first claim issued before the lengths are read, to overlap the two round
   // trips, was no faster on the listed shapes and 2 % slower on others.)
   const int n_queues = min(kQueues, args->batch * args->num_kv_heads);
-  int qx = (int)(blockIdx.x % (unsigned)n_queues);
+  int qx = (int)(blockIdx.x % (unsigned)(args->batch * args->num_kv_heads)) % kQueues;
   uint32_t open = (1u << n_queues) - 1u, entered = 0;
+  // What is known of the queue's groups (live_chunks; lane u: group u), read
+  // by the claim after one that turned out to be of no use.  With it, claims of
+  // further such chunks cost one atomic and no read, and the rest of a queue
+  // of stopped groups is dropped at once: walking through it, an atomic and
+  // two dependent reads per chunk, took the last 10 to 15 us of a launch
+  // over lists.
+  int live = 0x7fffffff, moot = 0;
+  bool stale = false;
 
   for (int it = 0;; ++it) {
     Params& P = *fresh(args);
+    const int n_groups = P.batch * P.num_kv_heads;
     const int slot = it % kSlots;
     if (lw == 0) {
       // leader: wait for the buffer, then claim the next chunk of the list
@@ -1883,33 +1936,48 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
         }
         __builtin_amdgcn_s_sleep(1);
       }
-      const int n_groups = P.batch * P.num_kv_heads;
       int gsel = -1, ksel = -1, len_sel = 0, list_sel = 0;
       while (!gave_up && open) {
         const int nx = (n_groups - qx + kQueues - 1) / kQueues;  // groups in queue qx
         const uint64_t claim = claim_issue(P, qx, !((entered >> qx) & 1u), lane);
         entered |= 1u << qx;
+        const uint64_t done = ld_relaxed(used_up_word(P));
         const int i = claim_finish(P, qx, claim, lane);
-        if (i >= nx * P.work_chunks) {
-          // this queue is used up: go on with the next one.  (Looking at
-          // all their words first, to pass over those that are used up as
-          // well, cost 7-9 % on launches of many groups: the reads meet the
-          // other workgroups' claims on the same lines.)
+        const int kh = i / nx, u = i - kh * nx;
+        bool used_up = i >= nx * P.work_chunks;
+        if (!used_up && stale) {
+          live = live_chunks(P, s_len, qx, nx, n_groups, lane);
+          stale = false;
+        }
+        if (!used_up && u < 64 && kh >= __builtin_amdgcn_readlane(live, u)) {
+          // a chunk known to be of no use: no read for it.  Now and then the
+          // stops are read again; once no group of the queue has a chunk of
+          // use in this row, the queue's word is moved to its end.
+          used_up = nx > 1 && nx <= 64 && !__any(kh < live);
+          if (!used_up) {
+            if (++moot % 8 == 0) stale = true;
+            continue;
+          }
+          if (lane == 0)
+            __hip_atomic_fetch_max(queue_word(P, qx), (P.epoch << kQueueBits) | (uint64_t)(nx * P.work_chunks),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (used_up) {
+          if (i == nx * P.work_chunks) mark_used_up(P, qx, lane);
+          // this queue is used up: go on with the next one that is not.
+          // (Looking at all the queues' own words for that cost 7-9 % on
+          // launches of many groups: the reads meet the other workgroups'
+          // claims on the same lines.)
           open &= ~(1u << qx);
+          open &= ~used_up_queues(P, done);
+          live = 0x7fffffff;
           if (open) {
             const uint32_t after = open & ~((2u << qx) - 1u);
             qx = __builtin_ctz(after ? after : open);
           }
           continue;
         }
-        int g = qx + kQueues * (i % nx);
-        const int kh = i / nx;
-        // Within every full run of kQueues groups, rotate by the run's
-        // index, so that each list mixes KV heads instead of holding one
-        // head's groups of every sequence (whose stops can fall close
-        // together and leave one list's workgroups with the late work).
-        // A bijection per list: every group still belongs to one list.
-        if (g / kQueues < n_groups / kQueues) g = (g / kQueues) * kQueues + (g % kQueues + g / kQueues) % kQueues;
+        const int g = queue_group(qx, u, n_groups);
         // the group's lengths (for a dense traversal of one of the first
         // kLenCache sequences from LDS, with no round trip); the loaders
         // check for a stop announced before the chunk with their page reads
@@ -1917,12 +1985,11 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
         const int L_raw = (bq < kLenCache && !P.block_list) ? lds_ld(&s_len[bq]) : P.seq_lens[bq];
         const int T_raw = raw_list_len(P, g);
         const GroupInfo gi = group_info_raw(P, g, L_raw, T_raw);
-        if (gi.n_chunks == 0) {
-          if (kh == 0) write_empty_wave<G>(P, gi.b, gi.kvh, lane);
+        if (gi.n_chunks == 0 && kh == 0) write_empty_wave<G>(P, gi.b, gi.kvh, lane);
+        if (kh >= gi.n_chunks || (P.block_list && stop_word_before(ld_relaxed(P.stop_word + g), P.epoch, kh))) {
+          stale = P.block_list || P.no_detector;  // (elsewhere the lengths, in LDS, tell it as fast)
           continue;
         }
-        if (kh >= gi.n_chunks) continue;
-        if (P.block_list && stop_word_before(ld_relaxed(P.stop_word + g), P.epoch, kh)) continue;
         gsel = g;
         ksel = kh;
         len_sel = L_raw;
@@ -2010,6 +2077,9 @@ __global__ void __launch_bounds__(kThreads, 2) art_decode_kernel(const KernelPar
       }
       if (stop_word_before(sw0, P.epoch, k)) {
         aborted = true;
+        // (with one group per queue the claims of its last chunks keep its
+        // workgroups from crowding the others: long_512k 208 us, 214 with)
+        stale = n_groups > kQueues;
       }
       for (int m = 0; m < n_my && !aborted; ++m) {
         const int i = lw + kLoaders * (m / tpb), j = m % tpb;
