@@ -343,6 +343,14 @@ art_status art_build_block_list(const art_decode_shape* shape, const art_list_op
                                 int32_t* block_list_len, double* block_scores,
                                 void* workspace, size_t workspace_bytes, hipStream_t stream);
 
+/* The same, and every entry of a row past its length is set to -1 (callers
+ * that hand out whole rows need no fill of their own before the call). */
+art_status art_build_block_list_padded(const art_decode_shape* shape, const art_list_opts* opts,
+                                       const void* q, const void* k_cache, const int32_t* page_table,
+                                       const int32_t* seq_lens, int32_t* block_list,
+                                       int32_t* block_list_len, double* block_scores,
+                                       void* workspace, size_t workspace_bytes, hipStream_t stream);
+
 #ifdef __cplusplus
 }
 #endif

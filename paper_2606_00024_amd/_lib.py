@@ -26,7 +26,7 @@ OUT_BF16 = 1
 EXPORTS = ("art_abi_version", "art_status_str", "art_decode_workspace_bytes",
            "art_workspace_init", "art_decode_attention", "art_validate_inputs",
            "art_workspace_status", "art_block_list_workspace_bytes", "art_build_block_list",
-           "art_decode_attention_static")
+           "art_decode_attention_static", "art_build_block_list_padded")
 STATIC_SCRATCH_BYTES = 64 << 20   # ART_STATIC_SCRATCH_BYTES
 
 LIST_IMPORTANCE = 0
@@ -118,10 +118,10 @@ def load_variant(path: str) -> ctypes.CDLL:
     lib.art_block_list_workspace_bytes.restype = ctypes.c_size_t
     lib.art_block_list_workspace_bytes.argtypes = [ctypes.POINTER(DecodeShape),
                                                    ctypes.POINTER(ListOpts), i32p]
-    lib.art_build_block_list.restype = ctypes.c_int
-    lib.art_build_block_list.argtypes = [
-        ctypes.POINTER(DecodeShape), ctypes.POINTER(ListOpts), vp, vp, vp, vp, vp, vp, vp,
-        vp, ctypes.c_size_t, vp]
+    for build in (lib.art_build_block_list, lib.art_build_block_list_padded):
+        build.restype = ctypes.c_int
+        build.argtypes = [ctypes.POINTER(DecodeShape), ctypes.POINTER(ListOpts), vp, vp, vp, vp, vp,
+                          vp, vp, vp, ctypes.c_size_t, vp]
     got = int(lib.art_abi_version())
     if got != ABI_VERSION:
         raise RuntimeError(f"{path} has ABI version {got}, this binding needs "
@@ -216,9 +216,11 @@ def block_list_workspace_bytes(shape: DecodeShape, opts: ListOpts) -> int:
 
 
 def build_block_list(shape, opts, q, k, page_table, seq_lens, block_list, block_list_len,
-                     block_scores, workspace, workspace_bytes, stream) -> int:
-    """Raw call; pointers are ints (0 for NULL).  Returns the status."""
-    return int(load().art_build_block_list(
+                     block_scores, workspace, workspace_bytes, stream, padded: bool = False) -> int:
+    """Raw call; pointers are ints (0 for NULL).  Returns the status.
+    ``padded``: entries past a row's length are set to -1 as well."""
+    call = load().art_build_block_list_padded if padded else load().art_build_block_list
+    return int(call(
         ctypes.byref(shape), ctypes.byref(opts), q or None, k or None, page_table or None,
         seq_lens, block_list, block_list_len, block_scores or None, workspace or None,
         workspace_bytes, stream or None))

@@ -225,17 +225,22 @@ def build_block_list(q: torch.Tensor, k_cache: torch.Tensor, page_table: torch.T
     if max_list is None:
         max_list = max(1, max_blocks)
     dev = q.device
-    bl = torch.full((B, Hkv, max_list), -1, dtype=torch.int32, device=dev)
-    bll = torch.zeros((B, Hkv), dtype=torch.int32, device=dev)
+    # the call writes every entry of the rows and every length
+    bl = torch.empty((B, Hkv, max_list), dtype=torch.int32, device=dev)
+    bll = torch.empty((B, Hkv), dtype=torch.int32, device=dev)
     shape = make_shape(q, k_cache, k_cache, page_table, block_size=block_size, block_list=bl)
     opts = _lib.ListOpts(policy=int(policy), score_kind=int(score_kind), budget=int(budget),
                          sink_blocks=int(sink_blocks), keep_last=1 if keep_last else 0)
     _lib.block_list_workspace_bytes(shape, opts)  # raises on invalid input
-    scores = torch.full((B, Hkv, max(1, max_blocks)), float("nan"), dtype=torch.float64,
-                        device=dev)
+    # scores of blocks past a sequence's end are not written: NaN for a caller
+    # who gets them, never read otherwise
+    scores = torch.empty((B, Hkv, max(1, max_blocks)), dtype=torch.float64, device=dev)
+    if return_scores:
+        scores.fill_(float("nan"))
     stream = torch.cuda.current_stream(dev).cuda_stream
     st = _lib.build_block_list(shape, opts, _ptr(q), _ptr(k_cache), _ptr(page_table),
-                               _ptr(seq_lens), _ptr(bl), _ptr(bll), _ptr(scores), 0, 0, stream)
+                               _ptr(seq_lens), _ptr(bl), _ptr(bll), _ptr(scores), 0, 0, stream,
+                               padded=True)
     if st != _lib.OK:
         raise ArtError(st, "art_build_block_list")
     return (bl, bll, scores) if return_scores else (bl, bll)

@@ -12,7 +12,7 @@
 //      products of bf16 values, so the scores do not depend on how the work
 //      is split: equal inputs give equal bits on any implementation that
 //      keeps that order.
-//   2. selection, one workgroup per group: a bitonic sort of (score, id)
+//   2. selection, one workgroup per group: a merge sort of (score, id)
 //      pairs in LDS, descending score and ascending id; the forced blocks
 //      (the first sink_blocks, and the last when asked) and the best others
 //      up to the budget are kept in sorted order.  Streaming lists need no
@@ -37,6 +37,7 @@ struct ListParams {
     int32_t max_pages, max_blocks, max_list, sort_n;
     int64_t ks_page, ks_head, ks_tok;
     int32_t policy, score_kind, budget, sink_blocks, keep_last;
+    int32_t pad;      // 1: entries past a row's length are set to -1
     const uint16_t* q;
     const uint16_t* k;
     const int32_t* page_table;
@@ -482,6 +483,47 @@ __device__ __forceinline__ void register_stages(double& k, int& i, bool up, int 
     if constexpr (S > 1) register_stages<S / 2>(k, i, up, lane);
 }
 
+// One round of a merge sort over the first `total` positions: neighbouring
+// runs of `run` sorted elements become runs of twice that.  An element's
+// place is its index in its own run plus the number of elements of the
+// neighbouring run that come before it, found by bisection; all places are
+// known before any element moves.  PER elements per thread.  (A bitonic
+// network over LDS took 45 barrier phases of compare-and-exchange for 2048
+// blocks, 20 us, all of it issue on one CU; the bisections are 45 dependent
+// LDS reads.)
+template <int PER>
+__device__ void merge_round(double* key, int* id, int total, int run) {
+    const int tid = threadIdx.x;
+    double k[PER];
+    int i[PER], at[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int p = min(tid + u * kListThreads, total - 1);
+        k[u] = key[p];
+        i[u] = id[p];
+        at[u] = (p & ~(run - 1)) ^ run;   // the neighbouring run, then the place in it
+    }
+    for (int step = run >> 1; step >= 1; step >>= 1)
+#pragma unroll
+        for (int u = 0; u < PER; ++u)
+            if (before(key[at[u] + step - 1], id[at[u] + step - 1], k[u], i[u])) at[u] += step;
+#pragma unroll
+    for (int u = 0; u < PER; ++u)
+        if (before(key[at[u]], id[at[u]], k[u], i[u])) ++at[u];
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int p = tid + u * kListThreads;
+        if (p < total) {
+            const int own = p & ~(run - 1);
+            const int to = (own & ~run) + (p - own) + (at[u] - (own ^ run));
+            key[to] = k[u];
+            id[to] = i[u];
+        }
+    }
+    __syncthreads();
+}
+
 __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int gidx = blockIdx.x, tid = threadIdx.x;
@@ -493,70 +535,47 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
         const int ns = min(P.sink_blocks, n);
         const int nr = min(P.budget, n - ns);
         for (int i = tid; i < ns + nr; i += kListThreads) out[i] = i < ns ? i : n - 1 - (i - ns);
+        if (P.pad)
+            for (int i = ns + nr + tid; i < P.max_list; i += kListThreads) out[i] = -1;
         if (tid == 0) P.list_len[gidx] = ns + nr;
         return;
     }
-    // importance: sort (score, id) pairs of blocks 0..n-1, padded to sort_n
-    const int N = P.sort_n;
+    // importance: sort (score, id) pairs of blocks 0..n-1 into descending
+    // score, ties by ascending id.  The elements that fill the sorted range
+    // up to a power of two come after them all and have ids of their own, and
+    // so do NaN scores' (unspecified, but the order must be total).
+    int N = 64;
+    while (N < n) N <<= 1;
     double* key = reinterpret_cast<double*>(lds);
-    int* id = reinterpret_cast<int*>(lds + (size_t)N * sizeof(double));
-    int* scratch = id + N;
+    int* id = reinterpret_cast<int*>(lds + (size_t)P.sort_n * sizeof(double));
+    int* scratch = id + P.sort_n;
     const double* sc = P.scores + (int64_t)gidx * P.max_blocks;
-    for (int i = tid; i < N; i += kListThreads) {
-        key[i] = i < n ? sc[i] : -INFINITY;
-        id[i] = i < n ? i : 0x7fffffff;
+    // Runs of 64 first, in registers: each wavefront takes whole segments
+    // (lane l holds position 64 s + l) through the bitonic stages, exchanging
+    // with lane l ^ stride (xor_lane).
+    const int wave = tid >> 6, lane = tid & 63;
+    for (int seg = wave; seg * 64 < N; seg += kListThreads / 64) {
+        const int pos = seg * 64 + lane;
+        double k = pos < n ? sc[pos] : -INFINITY;
+        if (!(k == k)) k = -INFINITY;
+        int i = pos;
+        register_stages<1>(k, i, (lane & 2) == 0, lane);
+        register_stages<2>(k, i, (lane & 4) == 0, lane);
+        register_stages<4>(k, i, (lane & 8) == 0, lane);
+        register_stages<8>(k, i, (lane & 16) == 0, lane);
+        register_stages<16>(k, i, (lane & 32) == 0, lane);
+        register_stages<32>(k, i, true, lane);
+        key[pos] = k;
+        id[pos] = i;
     }
     __syncthreads();
-    // Bitonic sort of positions 0..N-1 (N a power of two) into descending
-    // score, ties by ascending id.  Stages with a stride of 64 or more go
-    // through LDS, one pair per thread and a workgroup barrier each.  Stages
-    // below a stride of 64 never leave a 64-position segment: they run in
-    // registers, each wavefront taking whole segments (lane l holds position
-    // 64 s + l) and exchanging with lane l ^ stride (xor_lane), so that a
-    // segment is read and written once per run of such stages.  Sizes up to
-    // 64 have no other stages and run in a single pass.
-    const int wave = tid >> 6, lane = tid & 63;
-    auto segment_pass = [&](int size_from, int size_to) {
-        for (int seg = wave; seg * 64 < N; seg += kListThreads / 64) {
-            const int pos = seg * 64 + lane;
-            double k = pos < N ? key[pos] : -INFINITY;
-            int i = pos < N ? id[pos] : 0x7fffffff;
-            for (int size = size_from; size <= size_to; size <<= 1) {
-                const bool up = (pos & size) == 0;   // this run sorts "before" first
-                switch (min(size >> 1, 32)) {
-                    case 32: register_stages<32>(k, i, up, lane); break;
-                    case 16: register_stages<16>(k, i, up, lane); break;
-                    case 8: register_stages<8>(k, i, up, lane); break;
-                    case 4: register_stages<4>(k, i, up, lane); break;
-                    case 2: register_stages<2>(k, i, up, lane); break;
-                    default: register_stages<1>(k, i, up, lane); break;
-                }
-            }
-            if (pos < N) {
-                key[pos] = k;
-                id[pos] = i;
-            }
+    for (int run = 64; run < N; run <<= 1) {
+        switch (N / kListThreads) {
+            case 8: merge_round<8>(key, id, N, run); break;
+            case 4: merge_round<4>(key, id, N, run); break;
+            case 2: merge_round<2>(key, id, N, run); break;
+            default: merge_round<1>(key, id, N, run); break;
         }
-    };
-    segment_pass(2, min(N, 64));
-    __syncthreads();
-    for (int size = 128; size <= N; size <<= 1) {
-        for (int stride = size >> 1; stride >= 64; stride >>= 1) {
-            for (int p = tid; p < N / 2; p += kListThreads) {
-                const int i = (p / stride) * 2 * stride + (p % stride), j = i + stride;
-                const bool up = (i & size) == 0;
-                const double ki = key[i], kj = key[j];
-                const int ii = id[i], ij = id[j];
-                const bool swap = up ? before(kj, ij, ki, ii) : before(ki, ii, kj, ij);
-                if (swap) {
-                    key[i] = kj; key[j] = ki;
-                    id[i] = ij; id[j] = ii;
-                }
-            }
-            __syncthreads();
-        }
-        segment_pass(size, size);
-        __syncthreads();
     }
     // forced blocks and the budget for the others
     const int ns = min(P.sink_blocks, n);
@@ -595,6 +614,8 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
             if (take) out[pos++] = i;
         }
     }
+    if (P.pad)
+        for (int i = total_sel + tid; i < P.max_list; i += kListThreads) out[i] = -1;
     if (tid == 0) P.list_len[gidx] = total_sel;
 }
 
@@ -624,7 +645,7 @@ art_status check_list(const art_decode_shape* s, const art_list_opts* o, int& ma
     const int64_t mb = ((int64_t)s->max_pages_per_seq * s->page_size + s->block_size - 1) / s->block_size;
     if (mb > kMaxListBlocks) return ART_ERR_UNSUPPORTED;
     max_blocks = (int)mb;
-    sort_n = 1;
+    sort_n = 64;
     while (sort_n < max_blocks) sort_n <<= 1;
     // the longest list this call can write must fit a row
     int64_t longest;
@@ -641,22 +662,12 @@ art_status check_list(const art_decode_shape* s, const art_list_opts* o, int& ma
 }  // namespace
 }  // namespace art
 
-extern "C" {
+namespace {
 
-size_t art_block_list_workspace_bytes(const art_decode_shape* shape, const art_list_opts* opts,
-                                      int32_t* status) {
-    int mb = 0, sn = 0;
-    const art_status st = art::check_list(shape, opts, mb, sn);
-    if (status) *status = st;
-    if (st != ART_OK) return 0;
-    return (size_t)shape->batch * shape->num_kv_heads * mb * sizeof(double);
-}
-
-art_status art_build_block_list(const art_decode_shape* shape, const art_list_opts* opts,
-                                const void* q, const void* k_cache, const int32_t* page_table,
-                                const int32_t* seq_lens, int32_t* block_list,
-                                int32_t* block_list_len, double* block_scores, void* workspace,
-                                size_t workspace_bytes, hipStream_t stream) {
+art_status build_list(const art_decode_shape* shape, const art_list_opts* opts, const void* q,
+                      const void* k_cache, const int32_t* page_table, const int32_t* seq_lens,
+                      int32_t* block_list, int32_t* block_list_len, double* block_scores,
+                      void* workspace, size_t workspace_bytes, bool pad, hipStream_t stream) {
     using namespace art;
     int mb = 0, sn = 0;
     art_status st = check_list(shape, opts, mb, sn);
@@ -696,6 +707,7 @@ art_status art_build_block_list(const art_decode_shape* shape, const art_list_op
     P.budget = opts->budget;
     P.sink_blocks = opts->sink_blocks;
     P.keep_last = opts->keep_last;
+    P.pad = pad ? 1 : 0;
     P.q = static_cast<const uint16_t*>(q);
     P.k = static_cast<const uint16_t*>(k_cache);
     P.page_table = page_table;
@@ -726,6 +738,37 @@ art_status art_build_block_list(const art_decode_shape* shape, const art_list_op
                                   : 0;
     hipLaunchKernelGGL(select_kernel, dim3((unsigned)groups), dim3(kListThreads), lds, stream, P);
     return hipGetLastError() == hipSuccess ? ART_OK : ART_ERR_HIP;
+}
+}  // namespace
+
+extern "C" {
+
+size_t art_block_list_workspace_bytes(const art_decode_shape* shape, const art_list_opts* opts,
+                                      int32_t* status) {
+    int mb = 0, sn = 0;
+    const art_status st = art::check_list(shape, opts, mb, sn);
+    if (status) *status = st;
+    if (st != ART_OK) return 0;
+    return (size_t)shape->batch * shape->num_kv_heads * mb * sizeof(double);
+}
+
+art_status art_build_block_list(const art_decode_shape* shape, const art_list_opts* opts,
+                                const void* q, const void* k_cache, const int32_t* page_table,
+                                const int32_t* seq_lens, int32_t* block_list,
+                                int32_t* block_list_len, double* block_scores, void* workspace,
+                                size_t workspace_bytes, hipStream_t stream) {
+    return build_list(shape, opts, q, k_cache, page_table, seq_lens, block_list, block_list_len,
+                      block_scores, workspace, workspace_bytes, false, stream);
+}
+
+art_status art_build_block_list_padded(const art_decode_shape* shape, const art_list_opts* opts,
+                                       const void* q, const void* k_cache,
+                                       const int32_t* page_table, const int32_t* seq_lens,
+                                       int32_t* block_list, int32_t* block_list_len,
+                                       double* block_scores, void* workspace,
+                                       size_t workspace_bytes, hipStream_t stream) {
+    return build_list(shape, opts, q, k_cache, page_table, seq_lens, block_list, block_list_len,
+                      block_scores, workspace, workspace_bytes, true, stream);
 }
 
 }  // extern "C"
