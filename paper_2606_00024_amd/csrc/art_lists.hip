@@ -38,6 +38,7 @@ struct ListParams {
     int64_t ks_page, ks_head, ks_tok;
     int32_t policy, score_kind, budget, sink_blocks, keep_last;
     int32_t pad;      // 1: entries past a row's length are set to -1
+    int32_t packed;   // 1: the score kernels walk the blocks that hold tokens (see Walk)
     const uint16_t* q;
     const uint16_t* k;
     const int32_t* page_table;
@@ -74,8 +75,16 @@ constexpr int kTileLoads = 16;
 constexpr int kRowPitch = 272;   // bytes per token row in the LDS tile (256 + 16 of padding)
 
 // The score kernels are persistent: wavefront w walks the blocks w, w + W,
-// ... of the flattened (group, block) range (W = wavefronts in the grid),
-// skipping blocks past their sequence's end, one 64-token tile at a time.
+// ... (W = wavefronts in the grid), one 64-token tile at a time.  With up to
+// kListLenCache sequences these are the blocks that hold tokens, group after
+// group, so that every wavefront has the same share of them whatever the
+// lengths.  (Walking groups of max_blocks and skipping the blocks past their
+// sequence's end gave a wavefront the same few block indices of every group
+// where W is a multiple of max_blocks: the early ones of them all, or only
+// those of the longest sequences.  16 sequences of 2K to 64K tokens, 8 KV
+// heads: key norm 256 -> 239 us, query bound 278 -> 253; 8 of 4K to 32K, query
+// bound 69 -> 64; equal lengths 199 -> 202.)  Larger batches are walked that
+// way: their lengths are in no table a wavefront can search in one step.
 // The loads of the next tile are issued before the current tile is
 // processed, and the page ids two tiles ahead before that, so that every
 // wavefront keeps one tile of keys in flight while it computes.  Two things
@@ -88,24 +97,53 @@ constexpr int kRowPitch = 272;   // bytes per token row in the LDS tile (256 + 1
 constexpr int kListLenCache = 256;
 
 struct TilePos {
-    int64_t item;   // flattened group * max_blocks + block; >= n_items when done
+    int64_t item;   // position in the walk; >= n_items when done
     int gidx, b, kvh, blk, t0, j1;
 };
 
-__device__ __forceinline__ int cached_len(const ListParams& P, const int* s_len, int b) {
-    return b < kListLenCache ? s_len[b] : seq_len_of(P, b);
+// The walk's table: the lengths of the first kListLenCache sequences, and,
+// when they are all of them, where each sequence's blocks start in the walk.
+struct WalkTable {
+    int len[kListLenCache];
+    int start[kListLenCache];
+};
+struct Walk {
+    const WalkTable* table;      // in LDS
+    bool packed;                 // blocks that hold tokens only
+    int64_t stride, n_items;
+    int end[kListLenCache / 64]; // lane l: where the blocks of sequence l + 64 j end
+};
+
+__device__ __forceinline__ int cached_len(const ListParams& P, const Walk& W, int b) {
+    return b < kListLenCache ? W.table->len[b] : seq_len_of(P, b);
 }
 
 // The first tile of the first block at or after `item` that holds tokens.
-__device__ __forceinline__ TilePos first_tile(const ListParams& P, const int* s_len, int64_t item,
-                                              int64_t stride, int64_t n_items) {
+__device__ __forceinline__ TilePos first_tile(const ListParams& P, const Walk& W, int64_t item) {
     TilePos t;
     t.gidx = t.b = t.kvh = t.blk = t.t0 = 0;
     t.j1 = 1;
-    for (; item < n_items; item += stride) {
+    if (W.packed) {
+        if (item < W.n_items) {
+            // the sequences whose blocks end at or before the item come before its own
+            int b = 0;
+#pragma unroll
+            for (int j = 0; j < kListLenCache / 64; ++j) b += __popcll(__ballot(W.end[j] <= (int)item));
+            b = __builtin_amdgcn_readfirstlane(b);
+            const int L = __builtin_amdgcn_readfirstlane(W.table->len[b]);
+            const int r = (int)item - __builtin_amdgcn_readfirstlane(W.table->start[b]);
+            const int blocks = (L + P.block_size - 1) / P.block_size;
+            t.b = b; t.kvh = r / blocks; t.blk = r - t.kvh * blocks;
+            t.gidx = b * P.num_kv_heads + t.kvh;
+            t.t0 = t.blk * P.block_size; t.j1 = min(t.t0 + P.block_size, L);
+        }
+        t.item = item;
+        return t;
+    }
+    for (; item < W.n_items; item += W.stride) {
         const int gidx = (int)(item / P.max_blocks), blk = (int)(item % P.max_blocks);
         const int b = gidx / P.num_kv_heads;
-        const int L = cached_len(P, s_len, b);
+        const int L = cached_len(P, W, b);
         const int j0 = blk * P.block_size;
         if (j0 < L) {
             t.gidx = gidx; t.b = b; t.kvh = gidx % P.num_kv_heads; t.blk = blk;
@@ -117,14 +155,13 @@ __device__ __forceinline__ TilePos first_tile(const ListParams& P, const int* s_
     return t;
 }
 
-__device__ __forceinline__ TilePos next_tile(const ListParams& P, const int* s_len, TilePos t,
-                                             int64_t stride, int64_t n_items) {
-    if (t.item >= n_items) return t;
+__device__ __forceinline__ TilePos next_tile(const ListParams& P, const Walk& W, TilePos t) {
+    if (t.item >= W.n_items) return t;
     if (t.t0 + 64 < t.j1) {
         t.t0 += 64;
         return t;
     }
-    return first_tile(P, s_len, t.item + stride, stride, n_items);
+    return first_tile(P, W, t.item + W.stride);
 }
 
 // Page of 16-token piece (lane & 3) of the tile, in lane n (n < 4).  Every
@@ -164,11 +201,39 @@ __device__ __forceinline__ void wave_lds_fence() {
     __builtin_amdgcn_wave_barrier();
 }
 
-// Loads the lengths of the first kListLenCache sequences into LDS (every
-// thread of the workgroup takes part; a barrier follows).
-__device__ __forceinline__ void cache_lens(const ListParams& P, int* s_len) {
-    for (int i = threadIdx.x; i < min(P.batch, kListLenCache); i += blockDim.x) s_len[i] = seq_len_of(P, i);
+// Fills the walk's table (every thread of the workgroup takes part; a barrier
+// follows) and sets up this wavefront's walk.
+__device__ __forceinline__ Walk make_walk(const ListParams& P, WalkTable* table) {
+    const int lane = threadIdx.x & 63;
+    for (int i = threadIdx.x; i < min(P.batch, kListLenCache); i += blockDim.x) table->len[i] = seq_len_of(P, i);
     __syncthreads();
+    Walk W;
+    W.table = table;
+    W.packed = P.packed;
+    W.stride = (int64_t)gridDim.x * 4;
+    W.n_items = (int64_t)P.batch * P.num_kv_heads * P.max_blocks;
+    if (W.packed) {
+        // every wavefront sums the sequences' blocks itself, 64 at a time
+        int before = 0;
+#pragma unroll
+        for (int j = 0; j < kListLenCache / 64; ++j) {
+            const int b = 64 * j + lane;
+            const int own = b < P.batch ? (table->len[b] + P.block_size - 1) / P.block_size * P.num_kv_heads : 0;
+            int sum = own;
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int y = __shfl_up(sum, o);
+                if (lane >= o) sum += y;
+            }
+            W.end[j] = before + sum;
+            // (the wavefronts store the same values)
+            table->start[b] = before + sum - own;
+            before += __builtin_amdgcn_readlane(sum, 63);
+        }
+        W.n_items = before;
+        __syncthreads();
+    }
+    return W;
 }
 
 // Walks this wavefront's tiles with the loads one tile ahead; `pre_fn(t)`
@@ -177,15 +242,14 @@ __device__ __forceinline__ void cache_lens(const ListParams& P, int* s_len) {
 // `tile_fn(t, v)` consumes a tile, `block_fn(t)` ends a block (after its
 // last tile).
 template <class PreFn, class TileFn, class BlockFn>
-__device__ __forceinline__ void stream_tiles(const ListParams& P, const int* s_len, PreFn pre_fn,
+__device__ __forceinline__ void stream_tiles(const ListParams& P, const Walk& W, PreFn pre_fn,
                                              TileFn tile_fn, BlockFn block_fn) {
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int64_t stride = (int64_t)gridDim.x * 4;
-    const int64_t n_items = (int64_t)P.batch * P.num_kv_heads * P.max_blocks;
-    TilePos cur = first_tile(P, s_len, (int64_t)blockIdx.x * 4 + wave, stride, n_items);
+    const int64_t n_items = W.n_items;
+    TilePos cur = first_tile(P, W, (int64_t)blockIdx.x * 4 + wave);
     if (cur.item >= n_items) return;
-    TilePos nxt = next_tile(P, s_len, cur, stride, n_items);
+    TilePos nxt = next_tile(P, W, cur);
     const int pg_cur = tile_pages(P, cur, n_items, lane);
     int pg_nxt = tile_pages(P, nxt, n_items, lane);
     u32x4_l a[kTileLoads], b[kTileLoads];
@@ -193,7 +257,7 @@ __device__ __forceinline__ void stream_tiles(const ListParams& P, const int* s_l
     // One step: the page ids two tiles ahead, the keys of the next tile into
     // `nb`, then the current tile (in `cb`).  False once the work is done.
     auto step = [&](u32x4_l (&cb)[kTileLoads], u32x4_l (&nb)[kTileLoads]) -> bool {
-        const TilePos nn = next_tile(P, s_len, nxt, stride, n_items);
+        const TilePos nn = next_tile(P, W, nxt);
         const int pg_nn = tile_pages(P, nn, n_items, lane);
         pre_fn(cur);
         load_tile(P, nxt, pg_nxt, n_items, lane, nb);
@@ -218,12 +282,12 @@ constexpr int kKeyNormLds = 4 * 64 * kRowPitch;   // bytes per workgroup
 
 __global__ void __launch_bounds__(256) score_key_norm_kernel(const ListParams P) {
     extern __shared__ __align__(16) unsigned char tiles[];
-    __shared__ __align__(16) int s_len[kListLenCache];
-    cache_lens(P, s_len);
+    __shared__ WalkTable table;
+    const Walk W = make_walk(P, &table);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     unsigned char* tile = tiles + w * 64 * kRowPitch;
     double best = -1.0;   // below any sum of squares
-    stream_tiles(P, s_len, [](const TilePos&) {},
+    stream_tiles(P, W, [](const TilePos&) {},
         [&](const TilePos&, const u32x4_l (&v)[kTileLoads]) {
 #pragma unroll
             for (int i = 0; i < kTileLoads; ++i)
@@ -302,8 +366,8 @@ __device__ __forceinline__ void half_extremes(uint32_t smax, uint32_t smin, uint
 template <int G>
 __global__ void __launch_bounds__(256) score_query_bound_kernel(const ListParams P) {
     __shared__ double terms[4][G][128];
-    __shared__ __align__(16) int s_len[kListLenCache];
-    cache_lens(P, s_len);
+    __shared__ WalkTable table;
+    const Walk W = make_walk(P, &table);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     // word e of the lane's 16 bytes: dimensions 8c + 2e (low half), 8c + 2e + 1
     uint32_t smax[4], smin[4], umax[4], umin[4];
@@ -318,7 +382,7 @@ __global__ void __launch_bounds__(256) score_query_bound_kernel(const ListParams
     constexpr int QR = (G + 3) / 4;
     u32x4_l qw[QR];
     const int c = lane & 15, r = lane >> 4;
-    stream_tiles(P, s_len,
+    stream_tiles(P, W,
         [&](const TilePos& t) {
 #pragma unroll
             for (int h0 = 0, u = 0; h0 < G; h0 += 4, ++u) {
@@ -708,6 +772,8 @@ art_status build_list(const art_decode_shape* shape, const art_list_opts* opts, 
     P.sink_blocks = opts->sink_blocks;
     P.keep_last = opts->keep_last;
     P.pad = pad ? 1 : 0;
+    // the walk's positions are 32-bit (the stride is added to the last one)
+    P.packed = shape->batch <= kListLenCache && (int64_t)shape->batch * shape->num_kv_heads * mb < (1 << 30);
     P.q = static_cast<const uint16_t*>(q);
     P.k = static_cast<const uint16_t*>(k_cache);
     P.page_table = page_table;

@@ -196,3 +196,21 @@ def test_full_size_ragged_importance_lists():
         _compare(wl, host, OL.IMPORTANCE, kind, max_blocks // 4, 1, True)
     del wl, host
     torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("batch", [1, 64, 65, 256, 257])
+def test_ragged_walks(batch):
+    """The score kernels' walk over the blocks that hold tokens: sequences
+    around the 64 that one step of its search covers and the 256 of its
+    table (one more takes the general walk), the first, the last and runs in
+    the middle empty, more blocks than the launch has wavefronts."""
+    rng = np.random.default_rng(batch)
+    lens = rng.integers(1, 2500 if batch < 100 else 900, batch)
+    if batch > 1:
+        lens[[0, -1]] = 0
+        lens[batch // 3: batch // 3 + 5] = 0
+    host = small_workload(90 + batch, batch=batch, kv_heads=4, group=2,
+                          seq_len=tuple(int(x) for x in lens), block_size=64, page_size=16, needles=2)
+    wl = _to_dev(copy.copy(host))
+    for kind in (OL.KEY_NORM, OL.QUERY_BOUND):
+        _compare(wl, host, OL.IMPORTANCE, kind, 6, 1, True)
