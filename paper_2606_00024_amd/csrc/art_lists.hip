@@ -551,29 +551,34 @@ __device__ __forceinline__ void register_stages(double& k, int& i, bool up, int 
 // runs of `run` sorted elements become runs of twice that.  An element's
 // place is its index in its own run plus the number of elements of the
 // neighbouring run that come before it, found by bisection; all places are
-// known before any element moves.  PER elements per thread.  (A bitonic
-// network over LDS took 45 barrier phases of compare-and-exchange for 2048
-// blocks, 20 us, all of it issue on one CU; the bisections are 45 dependent
-// LDS reads.)
+// known before any element moves.  A run holds the ids of its own positions,
+// so that all ids of the lower run are the smaller ones: equal scores are told
+// apart by which run is which, and the bisection reads no ids.  PER elements
+// per thread.  (A bitonic network over LDS took 45 barrier phases of
+// compare-and-exchange for 2048 blocks, 20 us, all of it issue on one CU; the
+// bisections are 45 dependent LDS reads.)
 template <int PER>
 __device__ void merge_round(double* key, int* id, int total, int run) {
     const int tid = threadIdx.x;
     double k[PER];
     int i[PER], at[PER];
+    bool ties[PER];   // an equal score of the neighbouring run comes before it
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
         const int p = min(tid + u * kListThreads, total - 1);
         k[u] = key[p];
         i[u] = id[p];
         at[u] = (p & ~(run - 1)) ^ run;   // the neighbouring run, then the place in it
+        ties[u] = (p & run) != 0;
     }
+    auto precedes = [&](double other, int u) { return other > k[u] || (ties[u] && other == k[u]); };
     for (int step = run >> 1; step >= 1; step >>= 1)
 #pragma unroll
         for (int u = 0; u < PER; ++u)
-            if (before(key[at[u] + step - 1], id[at[u] + step - 1], k[u], i[u])) at[u] += step;
+            if (precedes(key[at[u] + step - 1], u)) at[u] += step;
 #pragma unroll
     for (int u = 0; u < PER; ++u)
-        if (before(key[at[u]], id[at[u]], k[u], i[u])) ++at[u];
+        if (precedes(key[at[u]], u)) ++at[u];
     __syncthreads();
 #pragma unroll
     for (int u = 0; u < PER; ++u) {
