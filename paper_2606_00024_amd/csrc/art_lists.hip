@@ -551,8 +551,8 @@ __device__ __forceinline__ void register_stages(double& k, int& i, bool up, int 
 // runs of `run` sorted elements become runs of twice that.  An element's
 // place is its index in its own run plus the number of elements of the
 // neighbouring run that come before it, found by bisection; all places are
-// known before any element moves.  A run holds the ids of its own positions,
-// so that all ids of the lower run are the smaller ones: equal scores are told
+// known before any element moves.  The elements are in id order before
+// the first round, so that all ids of the lower run are the smaller ones: equal scores are told
 // apart by which run is which, and the bisection reads no ids.  PER elements
 // per thread.  (A bitonic network over LDS took 45 barrier phases of
 // compare-and-exchange for 2048 blocks, 20 us, all of it issue on one CU; the
@@ -593,6 +593,82 @@ __device__ void merge_round(double* key, int* id, int total, int run) {
     __syncthreads();
 }
 
+// Blocks that can be on the list, in id order, into key[] and id[]; returns
+// how many (n, and nothing written, if that would be all of them).  The best
+// `need` blocks and the forced ones hold every entry of the list.  A
+// histogram of the scores' leading bits below the highest score (as ordered
+// integers, 128 bins per octave, the last one open) gives a bin at or above
+// which at least `need` blocks lie; equal scores share a bin, and a higher
+// score never has a later one.  What bounds the selection is its sorting on one
+// CU, so it pays where a third of the blocks or fewer are wanted of more than
+// 1024: 512 of 2048 blocks 19.3 -> 16.5 us, 512 of 8192 73 -> 20.
+constexpr int kFilterBlocks = 1024;
+constexpr int kFilterShift = 45;
+__device__ int keep_candidates(const double* sc, int n, int ns, bool last, int need, double* key, int* id,
+                               int* scratch) {
+    constexpr int kPer = kMaxListBlocks / kListThreads;
+    const int tid = threadIdx.x, lane = tid & 63;
+    int* bins = reinterpret_cast<int*>(key);   // one per thread; key[] holds more than kFilterBlocks entries
+    unsigned long long* top = reinterpret_cast<unsigned long long*>(id);
+    bins[tid] = 0;
+    if (tid == 0) *top = 0;
+    // consecutive blocks p0 .. p0 + per - 1 of each thread
+    const int per = (n + kListThreads - 1) / kListThreads, p0 = tid * per;
+    double s[kPer];
+    unsigned long long u[kPer], best = 0;
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        const int p = p0 + e;
+        s[e] = e < per && p < n ? sc[p] : -INFINITY;
+        if (!(s[e] == s[e])) s[e] = -INFINITY;
+        const unsigned long long w = (unsigned long long)__double_as_longlong(s[e] + 0.0);   // (-0 to +0)
+        u[e] = (long long)w < 0 ? ~w : w | (1ull << 63);
+        best = max(best, u[e]);
+    }
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) best = max(best, (unsigned long long)__shfl_xor((long long)best, o));
+    __syncthreads();
+    if (lane == 0) atomicMax(top, best);
+    __syncthreads();
+    best = *top >> kFilterShift;
+    int bin[kPer];
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) {
+        bin[e] = (int)min((unsigned long long)(kListThreads - 1), best - (u[e] >> kFilterShift));
+        if (e < per && p0 + e < n) atomicAdd(&bins[bin[e]], 1);
+    }
+    __syncthreads();
+    const int own = bins[tid];
+    int total;
+    const int above = block_exclusive_scan(own, scratch, total);
+    // (the scan's last barrier is behind every read of the bins and the top)
+    if (above < need && above + own >= need) *id = tid;
+    __syncthreads();
+    const int at = *id;
+    __syncthreads();
+    int cnt = 0;
+    auto wanted = [&](int e) {
+        const int p = p0 + e;
+        return e < per && p < n && (bin[e] <= at || p < ns || (last && p == n - 1));
+    };
+#pragma unroll
+    for (int e = 0; e < kPer; ++e) cnt += wanted(e) ? 1 : 0;
+    int pos = block_exclusive_scan(cnt, scratch, total);
+    if (total < n) {
+#pragma unroll
+        for (int e = 0; e < kPer; ++e)
+            if (wanted(e)) {
+                key[pos] = s[e];
+                id[pos++] = p0 + e;
+            }
+    }
+    __syncthreads();
+    return total;
+}
+
+// FILTER: rows may hold more than kFilterBlocks blocks (without that code the
+// selection of up to 1024 blocks takes 8.8 us in place of 9.4).
+template <bool FILTER>
 __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P) {
     extern __shared__ __align__(16) unsigned char lds[];
     const int gidx = blockIdx.x, tid = threadIdx.x;
@@ -609,25 +685,40 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
         if (tid == 0) P.list_len[gidx] = ns + nr;
         return;
     }
-    // importance: sort (score, id) pairs of blocks 0..n-1 into descending
-    // score, ties by ascending id.  The elements that fill the sorted range
-    // up to a power of two come after them all and have ids of their own, and
-    // so do NaN scores' (unspecified, but the order must be total).
-    int N = 64;
-    while (N < n) N <<= 1;
+    // forced blocks and the budget for the others
+    const int ns = min(P.sink_blocks, n);
+    const int nf = ns + ((P.keep_last && n > 0 && n - 1 >= ns) ? 1 : 0);
+    const int others = max(0, P.budget - nf);
+    // importance: sort (score, id) pairs of blocks 0..n-1, or of those of them
+    // that can be kept, into descending score, ties by ascending id.  The
+    // elements that fill the sorted range up to a power of two come after
+    // them all and have ids of their own, and so do NaN scores' (unspecified,
+    // but the order must be total).
     double* key = reinterpret_cast<double*>(lds);
     int* id = reinterpret_cast<int*>(lds + (size_t)P.sort_n * sizeof(double));
     int* scratch = id + P.sort_n;
     const double* sc = P.scores + (int64_t)gidx * P.max_blocks;
+    int m = n;
+    if constexpr (FILTER) {
+        const int need = max(1, max(P.budget, nf));
+        if (n > kFilterBlocks && need <= n / 3) m = keep_candidates(sc, n, ns, P.keep_last != 0, need, key, id, scratch);
+    }
+    const bool filtered = FILTER && m < n;
+    int N = 64;
+    while (N < m) N <<= 1;
     // Runs of 64 first, in registers: each wavefront takes whole segments
     // (lane l holds position 64 s + l) through the bitonic stages, exchanging
     // with lane l ^ stride (xor_lane).
     const int wave = tid >> 6, lane = tid & 63;
     for (int seg = wave; seg * 64 < N; seg += kListThreads / 64) {
         const int pos = seg * 64 + lane;
-        double k = pos < n ? sc[pos] : -INFINITY;
+        double k = -INFINITY;
+        int i = kMaxListBlocks + pos;   // (past every block's id)
+        if (pos < m) {
+            k = filtered ? key[pos] : sc[pos];
+            i = filtered ? id[pos] : pos;
+        }
         if (!(k == k)) k = -INFINITY;
-        int i = pos;
         register_stages<1>(k, i, (lane & 2) == 0, lane);
         register_stages<2>(k, i, (lane & 4) == 0, lane);
         register_stages<4>(k, i, (lane & 8) == 0, lane);
@@ -646,15 +737,11 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
             default: merge_round<1>(key, id, N, run); break;
         }
     }
-    // forced blocks and the budget for the others
-    const int ns = min(P.sink_blocks, n);
-    const int nf = ns + ((P.keep_last && n > 0 && n - 1 >= ns) ? 1 : 0);
-    const int others = max(0, P.budget - nf);
     // each thread takes a run of consecutive sorted positions
     const int per = (N + kListThreads - 1) / kListThreads;
     const int p0 = tid * per;
     int cnt_other = 0;
-    for (int p = p0; p < min(p0 + per, n); ++p) {
+    for (int p = p0; p < min(p0 + per, m); ++p) {
         const int i = id[p];
         const bool forced = i < ns || (P.keep_last && i == n - 1);
         cnt_other += forced ? 0 : 1;
@@ -664,7 +751,7 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
     int cnt_sel = 0;
     {
         int r = rank_other;
-        for (int p = p0; p < min(p0 + per, n); ++p) {
+        for (int p = p0; p < min(p0 + per, m); ++p) {
             const int i = id[p];
             const bool forced = i < ns || (P.keep_last && i == n - 1);
             if (forced) ++cnt_sel;
@@ -675,7 +762,7 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
     int pos = block_exclusive_scan(cnt_sel, scratch, total_sel);
     {
         int r = rank_other;
-        for (int p = p0; p < min(p0 + per, n); ++p) {
+        for (int p = p0; p < min(p0 + per, m); ++p) {
             const int i = id[p];
             const bool forced = i < ns || (P.keep_last && i == n - 1);
             bool take = forced;
@@ -807,7 +894,8 @@ art_status build_list(const art_decode_shape* shape, const art_list_opts* opts, 
     const size_t lds = importance ? (size_t)sn * (sizeof(double) + sizeof(int)) +
                                         (kListThreads / 64 + 1) * sizeof(int)
                                   : 0;
-    hipLaunchKernelGGL(select_kernel, dim3((unsigned)groups), dim3(kListThreads), lds, stream, P);
+    auto select = importance && mb > kFilterBlocks ? select_kernel<true> : select_kernel<false>;
+    hipLaunchKernelGGL(select, dim3((unsigned)groups), dim3(kListThreads), lds, stream, P);
     return hipGetLastError() == hipSuccess ? ART_OK : ART_ERR_HIP;
 }
 }  // namespace

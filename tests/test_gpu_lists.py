@@ -214,3 +214,29 @@ def test_ragged_walks(batch):
     wl = _to_dev(copy.copy(host))
     for kind in (OL.KEY_NORM, OL.QUERY_BOUND):
         _compare(wl, host, OL.IMPORTANCE, kind, 6, 1, True)
+
+
+@pytest.mark.parametrize("blocks", [1024, 1025, 2047, 4100, 8192])
+def test_selection_of_few_blocks(blocks):
+    """Rows around the 1024 blocks above which the selection sorts only the
+    candidates of its histogram, and budgets around the third of a row where
+    it does so: ordinary scores, scores of many octaves (the histogram's open
+    last bin), many equal ones, all equal, and negative ones; the forced
+    blocks below the threshold."""
+    host = small_workload(200 + blocks, batch=5, kv_heads=1, group=2, block_size=64, page_size=64,
+                          seq_len=(blocks * 64, blocks * 64 - 1, blocks * 64, blocks * 64, 64 * 900), needles=2)
+    k = torch.where(host.k_cache.isnan(), torch.zeros((), dtype=host.k_cache.dtype), host.k_cache)
+    pages = [host.page_table[b, :blocks].long() for b in range(4)]
+    gen = torch.Generator().manual_seed(blocks)
+    scale = 2.0 ** torch.randint(-12, 12, (blocks,), generator=gen)
+    k[pages[1]] *= scale[:, None, None, None].to(k.dtype)
+    k[pages[2]] = k[pages[2]][:1] * (2.0 ** torch.randint(0, 2, (blocks,), generator=gen))[:, None, None, None].to(k.dtype)
+    k[pages[3]] = -k[pages[3]].abs()
+    host.q[3] = host.q[3].abs()          # every query bound of this row is negative
+    host.q[2, 0] = 0
+    host.k_cache = k
+    wl = _to_dev(copy.copy(host))
+    for kind in (OL.KEY_NORM, OL.QUERY_BOUND):
+        for budget, sinks, last in ((0, 0, False), (1, 0, True), (60, 4, True), (blocks // 3 - 1, 1, True),
+                                    (blocks // 3, 0, False), (blocks // 3 + 1, 2, True), (3, blocks // 4, True)):
+            _compare(wl, host, OL.IMPORTANCE, kind, budget, sinks, last)
