@@ -8,8 +8,8 @@
 //
 // Work decomposition
 //   A group's traversal of T blocks is cut into chunks of consecutive
-//   blocks (with the default plan, four leading chunks of 3 blocks, then
-//   chunks of C).  The chunks of all groups form eight chunk-major work lists
+//   blocks (with the default plan, leading chunks of 3 blocks, then chunks
+//   of C).  The chunks of all groups form eight chunk-major work lists
 //   (list x holds the groups 8r + (x + r) mod 8 of every full run r of eight
 //   groups, and the leftover groups g with g mod 8 = x: chunk 0 of each, then
 //   chunk 1, ...).  The grid is persistent (as many workgroups as the chip holds);

@@ -446,16 +446,23 @@ __global__ void __launch_bounds__(256) score_query_bound_kernel(const ListParams
 
 // A persistent launch of 256-thread workgroups: as many as are resident at
 // once (never more than one wavefront per work item), so that no workgroup
-// waits for another to finish before it starts its share.
+// waits for another to finish before it starts its share.  With `spread`,
+// four times as many once a wavefront would have 32 tiles or more: the chip
+// hands the shares out as others end, which evens out CUs that run ahead
+// (key norm of 4 x 128K 203 -> 193 us, 1 x 512K 198 -> 193, 16 ragged
+// sequences of up to 64K 241 -> 234; with 16 tiles each 103 -> 104).  The query
+// bound's wavefronts cost more to start: 204 -> 213 us on the first.
 template <class Kernel>
-hipError_t launch_persistent(Kernel kernel, int64_t items, size_t lds, hipStream_t stream, const ListParams& P) {
+hipError_t launch_persistent(Kernel kernel, int64_t items, size_t lds, hipStream_t stream, const ListParams& P,
+                             bool spread = false) {
     int dev = 0, cus = 0, per_cu = 0;
     hipError_t e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, 256, lds);
     if (e != hipSuccess) return e;
     if (per_cu < 1) per_cu = 1;
-    const int64_t grid = std::min<int64_t>((items + 3) / 4, (int64_t)cus * per_cu);
+    const int64_t resident = (int64_t)cus * per_cu, tiles = items * ((P.block_size + 63) / 64);
+    const int64_t grid = std::min<int64_t>((items + 3) / 4, spread && tiles >= 32 * 4 * resident ? 4 * resident : resident);
     hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(256), lds, stream, P);
     return hipGetLastError();
 }
@@ -877,7 +884,7 @@ art_status build_list(const art_decode_shape* shape, const art_list_opts* opts, 
     if (importance && (int64_t)groups * mb > 0) {
         const int64_t waves = (int64_t)groups * mb;
         if (opts->score_kind == ART_SCORE_KEY_NORM) {
-            if (launch_persistent(score_key_norm_kernel, waves, kKeyNormLds, stream, P) != hipSuccess)
+            if (launch_persistent(score_key_norm_kernel, waves, kKeyNormLds, stream, P, true) != hipSuccess)
                 return ART_ERR_HIP;
         } else {
             hipError_t e;
