@@ -218,6 +218,8 @@ __device__ __forceinline__ Walk make_walk(const ListParams& P, WalkTable* table)
 #pragma unroll
         for (int j = 0; j < kListLenCache / 64; ++j) {
             const int b = 64 * j + lane;
+            W.end[j] = before;
+            if (64 * j >= P.batch) continue;   // (no sequences: past every position of the walk)
             const int own = b < P.batch ? (table->len[b] + P.block_size - 1) / P.block_size * P.num_kv_heads : 0;
             int sum = own;
 #pragma unroll
