@@ -336,6 +336,7 @@ __device__ __forceinline__ bool slot_valid(int lane, int k) {
 // operations per output.  The results are those of merging one record after
 // the other, bit for bit, wherever a run is cut.  (Each record's exponentials
 // and their latency inside the step took the resolver 0.55 us a block.)
+static_assert(kMaxChunkBlocks <= 16, "a chunk's blocks fit the 16 lanes of a row");
 template <int G>
 struct Run {
   float m[Cfg<G>::HPL];    // lane (r, c): maximum after record c
@@ -366,7 +367,7 @@ __device__ __forceinline__ void run_factors(Run<G>& f, int k, float m0, float m,
   f.add[k] = v ? __fmul_rn(L, fast_exp2(__fsub_rn(m, x))) : 0.f;
 }
 
-// the value of lane i of this lane's row
+// the value of lane i < 16 of this lane's row
 __device__ __forceinline__ float row_lane(float x, int i, int lane) {
   return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * ((lane & 48) | i), __float_as_int(x)));
 }
@@ -432,6 +433,22 @@ __device__ __forceinline__ void read_masses(const float* blocks, int nb, int k, 
   L = c < nb ? rec[G] : 0.f;
 }
 
+// fn(i) for the blocks 0 .. nb - 1 in order, GANG of them at a time with no
+// branch between, so that their loads, weights and row sums overlap; the one
+// or two that are left one by one.  (Never a block past nb: its lane
+// may lie in another row, and a weight of zero times an infinite output is
+// no zero.)
+template <int G, class Fn>
+__device__ __forceinline__ void gangs_of_blocks(int nb, Fn fn) {
+  constexpr int GANG = Cfg<G>::GANG;
+  int i = 0;
+  for (; i + GANG <= nb; i += GANG)
+#pragma unroll
+    for (int u = 0; u < GANG; ++u) fn(i + u);
+#pragma unroll 1
+  for (; i < nb; ++i) fn(i);
+}
+
 // The chunk's aggregate: the state of its blocks alone.  The weights of all
 // blocks come at once (lane (r, c): block c), then one fused multiply-add
 // per block and output.
@@ -452,19 +469,16 @@ __device__ __forceinline__ void aggregate(State<G>& s, const float* blocks, int 
 #pragma unroll
     for (int e = 0; e < 8; ++e) s.o[k][e] = 0.f;
   }
-  // (blocks past nb read the last one's record with weight 0)
-  for (int i0 = 0; i0 < nb; i0 += Cfg<G>::GANG) {
+  gangs_of_blocks<G>(nb, [&](int i) {
 #pragma unroll
-    for (int u = 0; u < Cfg<G>::GANG; ++u)
+    for (int k = 0; k < HPL; ++k) {
+      float p[8];
+      read_output<G>(blocks + i * Cfg<G>::REC, k, lane, p);
+      const float wi = row_lane(w[k], i, lane);
 #pragma unroll
-      for (int k = 0; k < HPL; ++k) {
-        float p[8];
-        read_output<G>(blocks + min(i0 + u, nb - 1) * Cfg<G>::REC, k, lane, p);
-        const float wi = row_lane(w[k], i0 + u, lane);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s.o[k][e] = __builtin_fmaf(wi, p[e], s.o[k][e]);
-      }
-  }
+      for (int e = 0; e < 8; ++e) s.o[k][e] = __builtin_fmaf(wi, p[e], s.o[k][e]);
+    }
+  });
 }
 
 // Workspace records go through a buffer resource over the group's record
@@ -1675,8 +1689,8 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
   // Replay the chunk's blocks from the prefix with the stability test.  The
   // steps run in order (each needs the state after the previous block); the
   // row sums of |d|^2 and o(t-1).d of block i stay in lane c = i of the
-  // head's row with |o(t-1)|^2 (blocks past the chunk's last add nothing and
-  // are masked out below), and |o(t)|^2 follows as
+  // head's row with |o(t-1)|^2 (lanes past the chunk's last block are
+  // masked out below), and |o(t)|^2 follows as
   // |o(t-1)|^2 + 2 o(t-1).d + |d|^2.  The verdicts of all blocks and heads
   // are then taken at once, lane (r, c) for block c of head r + 4k.  (One
   // verdict after the other and merges with their exponentials inside took
@@ -1713,7 +1727,7 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
     // step i of slot kk; the sums it leaves in lane c = i
     auto step = [&](int i, int kk, bool plain) {
       float p[8], d[8], o0[8];
-      read_output<G>(blocks + min(i, nb - 1) * REC, kk, lane, p);
+      read_output<G>(blocks + i * REC, kk, lane, p);
       const float L0 = s.L[kk];
 #pragma unroll
       for (int e = 0; e < 8; ++e) o0[e] = s.o[kk][e];
@@ -1748,13 +1762,10 @@ __device__ void resolve_chunk(Params& P, int gidx, int k, const GroupInfo& gi,
       if (c == i) acc_dx[kk] = dx2;
     };
     if (full_probe && !on_acc) {
-      // (no branch between the steps of a gang: their loads, weights and row
-      // sums overlap)
-      for (int i0 = 0; i0 < nb; i0 += Cfg<G>::GANG)
+      gangs_of_blocks<G>(nb, [&](int i) {
 #pragma unroll
-        for (int u = 0; u < Cfg<G>::GANG; ++u)
-#pragma unroll
-          for (int kk = 0; kk < HPL; ++kk) step(i0 + u, kk, true);
+        for (int kk = 0; kk < HPL; ++kk) step(i, kk, true);
+      });
     } else {
 #pragma unroll 1
       for (int i = 0; i < nb; ++i)
