@@ -98,9 +98,10 @@ typedef struct {
  * removes that half of the test (the ablations of Table 3).  patience >= 1;
  * patience = 1 is "no patience"; INT32_MAX runs the detector without ever
  * stopping.  chunk_blocks = 0 lets the library pick the split of each
- * traversal into chunks from the shape, the order and no_detector alone
- * (never from the data or the thresholds: with the test, short leading chunks
- * of 3 blocks, then chunks of up to 9; without it, chunks of up to 12);
+ * traversal into chunks from the shape, the kind of walk (order, list or
+ * none, no_detector) and whether the workspace holds art_decode_workspace_bytes()
+ * alone (never from the data or the thresholds: with the test, short leading
+ * chunks of 3 blocks, then chunks of up to 9; without it, chunks of up to 12);
  * 1..16 asks for that many blocks in every chunk (capped at what the
  * shared-memory budget holds for the shape).  The chunking changes
  * rounding only.
@@ -165,8 +166,12 @@ int32_t art_abi_version(void);
 const char* art_status_str(int32_t status);
 
 /*
- * Workspace bytes the call with this shape and these options needs (a
- * function of the shape only).  Returns 0 and sets *status on invalid input.
+ * Workspace bytes that calls of this shape need: a function of the shape,
+ * chunk_blocks and whether there are per-head stops, the same for every other
+ * option, with and without a list.  Returns 0 and sets *status on invalid
+ * input.  (A call also runs in as many bytes as its longest chunks take, which
+ * is what a program has that sized its workspace for longer sequences than the
+ * call's; then those are the chunks.)
  */
 size_t art_decode_workspace_bytes(const art_decode_shape* shape,
                                   const art_decode_opts* opts, int32_t* status);

@@ -1,6 +1,6 @@
 // Host side of the C ABI declared in include/art.h: argument checks, the
-// launch plan (a function of the shape only), the workspace layout, the
-// per-call epoch and the checked-mode validator.
+// launch plan (a function of the shape and the kind of walk), the workspace
+// layout, the per-call epoch and the checked-mode validator.
 #include "art.h"
 
 #include <math.h>
@@ -91,11 +91,23 @@ art_status check_shape(const art_decode_shape* s, const art_decode_opts* o) {
     return ART_OK;
 }
 
-// Everything about the launch is decided here from the shape and the options
-// (chunk_blocks, the order, whether the test runs): never from the data or
-// the thresholds.  `compact` keeps to the longest chunks and the fewest
-// leading ones (see make_plan).
-art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool compact, Plan* p) {
+// The kinds of walk that are planned apart.
+struct Walk {
+    bool detector;  // the stability test runs
+    bool early;     // and tends to stop the walk soon (see walk_of)
+};
+
+// Walks that tend to stop early: lists and oldest-first walks (the sinks
+// first) of groups of few heads.
+Walk walk_of(const art_decode_shape* s, const art_decode_opts* o, bool listed) {
+    const bool early = s->num_q_heads / s->num_kv_heads <= 4 && (listed || o->dense_order == ART_ORDER_FORWARD);
+    return Walk{!o->no_detector, !o->no_detector && early};
+}
+
+// Everything about the launch is decided here from the shape, chunk_blocks
+// and the kind of walk: never from the data or the thresholds.  `compact`
+// keeps to the longest chunks and the fewest leading ones (see choose_plan).
+art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, Walk walk, bool compact, Plan* p) {
     const int g = s->num_q_heads / s->num_kv_heads;
     const int tpb = s->block_size / art::kTile;
     const int64_t cap_tokens = (int64_t)s->max_pages_per_seq * s->page_size;
@@ -124,10 +136,6 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool
     while (c_max > 1 && (c_max + 2) / 3 * tpb > art::kMaxChunkTiles) --c_max;
     if (c_max < 1) return ART_ERR_UNSUPPORTED;
 
-    // walks that tend to stop early: lists (best blocks first) and oldest-first
-    // walks (the sinks first) of groups of few heads
-    const bool early = !compact && !o->no_detector && g <= 4 &&
-                       (s->max_blocks_per_list > 0 || o->dense_order == ART_ORDER_FORWARD);
     int C;
     if (o->chunk_blocks > 0) {
         C = o->chunk_blocks;
@@ -142,7 +150,7 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool
         // chunk whenever there were fewer chunks than 1024 cost 17-210 % on
         // problems of 2 to 16 groups; the per-chunk work of the resolver
         // outweighs the wider spread.)
-        const int most = o->no_detector ? 12 : 9;
+        const int most = walk.detector ? 9 : 12;
         C = c_max < most ? c_max : most;
         if (C >= 3) C -= C % 3;
         while (C > 3 && (n_groups * ((t_cap + C - 1) / C) < 64 || (!compact && 5 * C > t_cap))) C -= 3;
@@ -159,8 +167,8 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool
     // recency-first batch of 8 x 32K, which stops later, 132 / 130 / 128.
     // Without the test there is nothing to decide.
     int lead_chunks = 0, lead_blocks = C;
-    if (o->chunk_blocks == 0 && C > kLeadBlocks && !o->no_detector) {
-        lead_chunks = early ? kLeadChunksEarly : kLeadChunks;
+    if (o->chunk_blocks == 0 && C > kLeadBlocks && walk.detector) {
+        lead_chunks = walk.early && !compact ? kLeadChunksEarly : kLeadChunks;
         lead_blocks = kLeadBlocks;
     }
     // Workgroups per group, at most (never fewer than one per CU): beyond
@@ -169,7 +177,7 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool
     // groups take 56 us in place of 75 on the 25 % lists and 39 in place of 52
     // oldest-first, 87 in place of 92 recency-first at 4 x 32K tokens; if none
     // of those stops, 125 in place of 118.
-    p->group_workgroups = o->no_detector || g > 4 ? 32 : 8;
+    p->group_workgroups = !walk.detector || g > 4 ? 32 : 8;
     p->lead_chunks = lead_chunks;
     p->lead_blocks = lead_blocks;
     const int64_t max_chunks = chunks_for(t_cap, C, lead_chunks, lead_blocks);
@@ -200,32 +208,53 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, bool
     return ART_OK;
 }
 
-// The plan of a call.  Short leading chunks and short chunks cost workspace:
-// where only they would take a shape past the library's own scratch, or past
-// what the queue words and record offsets hold, it keeps the compact plan.
-art_status make_plan(const art_decode_shape* s, const art_decode_opts* o, Plan* p) {
-    art_status st = check_shape(s, o);
-    if (st != ART_OK) return st;
-    st = plan_chunks(s, o, false, p);
-    if (st != ART_OK || p->ws.total > ART_STATIC_SCRATCH_BYTES) {
-        Plan compact;
-        const art_status sc = plan_chunks(s, o, true, &compact);
-        if (sc == ART_OK && (st != ART_OK || compact.ws.total <= ART_STATIC_SCRATCH_BYTES)) {
-            *p = compact;
-            st = sc;
-        }
+// The plan of a kind of walk.  Short leading chunks and short chunks cost
+// workspace: where only they would take a shape past the library's own
+// scratch, or past what the queue words and record offsets hold, it keeps the
+// compact plan.
+art_status choose_plan(const art_decode_shape* s, const art_decode_opts* o, Walk walk, Plan* p) {
+    const art_status st = plan_chunks(s, o, walk, false, p);
+    if (st == ART_OK && p->ws.total <= ART_STATIC_SCRATCH_BYTES) return st;
+    Plan compact;
+    const art_status sc = plan_chunks(s, o, walk, true, &compact);
+    if (sc == ART_OK && (st != ART_OK || compact.ws.total <= ART_STATIC_SCRATCH_BYTES)) {
+        *p = compact;
+        return sc;
     }
     return st;
 }
 
-// Host checks of a decode call and its plan (everything but the workspace).
+// Workspace bytes of a shape: `need`, the most that the plan of any kind of
+// walk takes, so that one workspace serves every order, lists or none, with
+// and without the test; and `least`, what the compact plan of a walk with the
+// test takes: a call that gets so much runs, if need be with that plan (a
+// program may size its workspace for its longest sequences, and the plan of
+// shorter ones can take more: 44 blocks in chunks of 6, 48 in chunks of 9).
+art_status workspace_of(const art_decode_shape* s, const art_decode_opts* o, size_t* need, size_t* least) {
+    art_status st = check_shape(s, o);
+    if (st != ART_OK) return st;
+    Plan p;
+    st = plan_chunks(s, o, Walk{true, false}, true, &p);
+    if (st != ART_OK) return st;
+    *need = *least = p.ws.total;
+    for (const Walk walk : {Walk{true, false}, Walk{true, true}, Walk{false, false}}) {
+        st = choose_plan(s, o, walk, &p);
+        if (st != ART_OK) return st;
+        if (p.ws.total > *need) *need = p.ws.total;
+    }
+    return ART_OK;
+}
+
+// Host checks of a decode call, and its plan within `bytes` of workspace
+// (`scratch`: the library's own, for shapes whose workspace it holds).
 art_status check_decode_call(const art_decode_shape* shape, const art_decode_opts* opts,
                              const void* q, const void* k_cache, const void* v_cache,
                              const int32_t* page_table, const int32_t* seq_lens,
                              const int32_t* block_list, const int32_t* block_list_len,
                              const void* out, const float* lse, const int32_t* stop_block,
-                             Plan* plan) {
-    art_status st = make_plan(shape, opts, plan);
+                             size_t bytes, bool scratch, Plan* plan) {
+    size_t need = 0, least = 0;
+    art_status st = workspace_of(shape, opts, &need, &least);
     if (st != ART_OK) return st;
     if (shape->batch == 0) return ART_OK;
     if (!q || !k_cache || !v_cache || !page_table || !seq_lens || !out || !lse || !stop_block)
@@ -234,7 +263,11 @@ art_status check_decode_call(const art_decode_shape* shape, const art_decode_opt
     if (block_list && shape->max_blocks_per_list <= 0) return ART_ERR_INVALID_ARG;
     if (((uintptr_t)q | (uintptr_t)k_cache | (uintptr_t)v_cache | (uintptr_t)out) % 16)
         return ART_ERR_UNSUPPORTED;
-    return ART_OK;
+    if (bytes < (scratch ? need : least)) return ART_ERR_WORKSPACE_TOO_SMALL;
+    const Walk walk = walk_of(shape, opts, block_list != nullptr);
+    st = choose_plan(shape, opts, walk, plan);
+    if (st == ART_OK && plan->ws.total > bytes) st = plan_chunks(shape, opts, Walk{true, false}, true, plan);
+    return st;
 }
 
 // Kernel parameters of a checked call over the workspace at `workspace`,
@@ -336,10 +369,10 @@ const char* art_status_str(int32_t status) {
 
 size_t art_decode_workspace_bytes(const art_decode_shape* shape, const art_decode_opts* opts,
                                   int32_t* status) {
-    Plan p;
-    art_status st = make_plan(shape, opts, &p);
+    size_t need = 0, least = 0;
+    const art_status st = workspace_of(shape, opts, &need, &least);
     if (status) *status = st;
-    return st == ART_OK ? p.ws.total : 0;
+    return st == ART_OK ? need : 0;
 }
 
 art_status art_workspace_init(void* workspace, size_t bytes, hipStream_t stream) {
@@ -357,9 +390,9 @@ art_status art_decode_attention(const art_decode_shape* shape, const art_decode_
                                 void* workspace, size_t workspace_bytes, hipStream_t stream) {
     Plan plan;
     art_status st = check_decode_call(shape, opts, q, k_cache, v_cache, page_table, seq_lens,
-                                      block_list, block_list_len, out, lse, stop_block, &plan);
+                                      block_list, block_list_len, out, lse, stop_block,
+                                      workspace ? workspace_bytes : 0, false, &plan);
     if (st != ART_OK || shape->batch == 0) return st;
-    if (!workspace || workspace_bytes < plan.ws.total) return ART_ERR_WORKSPACE_TOO_SMALL;
     if ((uintptr_t)workspace % 8) return ART_ERR_INVALID_ARG;
     return enqueue_decode(plan, shape, opts, q, k_cache, v_cache, page_table, seq_lens,
                           block_list, block_list_len, out, lse, stop_block, workspace, stream);
@@ -373,9 +406,9 @@ art_status art_decode_attention_static(const art_decode_shape* shape, const art_
                                        hipStream_t stream) {
     Plan plan;
     art_status st = check_decode_call(shape, opts, q, k_cache, v_cache, page_table, seq_lens,
-                                      block_list, block_list_len, out, lse, stop_block, &plan);
+                                      block_list, block_list_len, out, lse, stop_block,
+                                      ART_STATIC_SCRATCH_BYTES, true, &plan);
     if (st != ART_OK || shape->batch == 0) return st;
-    if (plan.ws.total > ART_STATIC_SCRATCH_BYTES) return ART_ERR_WORKSPACE_TOO_SMALL;
     void* scratch = nullptr;
     if (art::static_scratch(stream, &scratch) != (int)hipSuccess) return ART_ERR_HIP;
     return enqueue_decode(plan, shape, opts, q, k_cache, v_cache, page_table, seq_lens,

@@ -11,6 +11,7 @@ import torch
 
 from helpers import random_lists, small_workload
 from parity import compare_workload, host_copy
+from test_plan_workspace import _compact_chunks
 from paper_2606_00024_amd import _lib, api
 
 pytestmark = pytest.mark.gpu
@@ -78,3 +79,34 @@ def test_rows_far_apart(group):
     assert not rep.failures, rep.failures[:3]
     for a, b in zip(near, far_out):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("group", [1, 4, 8])
+def test_small_workspace(group):
+    """A workspace of the bytes that the longest chunks take, and not a byte
+    more: every kind of walk runs in it, one after the other, and leaves what
+    lies behind it alone."""
+    lens = tuple(64 * 44 - 7 * b for b in range(16))
+    wl = small_workload(72, batch=16, kv_heads=4, group=group, seq_len=lens, device=DEV)
+    least, tail = _compact_chunks(group, 64, 44, 64)[1], 1 << 16
+    buf = api.new_workspace(least + tail, DEV)
+    buf[least:] = 0x5A
+    lists = random_lists(wl, 5, fraction=0.9)
+    host = host_copy(wl)
+    ran_short = 0
+    for kw in (dict(tau=1e-3, phi=1e-4, patience=5), dict(tau=0.0, phi=1e-4, patience=5)):
+        for listed in (False, True):
+            wl.block_list, wl.block_list_len = (x.to(DEV) for x in lists) if listed else (None, None)
+            host.block_list, host.block_list_len = lists if listed else (None, None)
+            for order in (0, 1):
+                for off in (False, True):
+                    if off and kw["tau"] > 0.0:
+                        continue
+                    gpu = api.decode_workload(wl, workspace=buf[:least], dense_order=order, no_detector=off, **kw)
+                    again = api.decode_workload(wl, dense_order=order, no_detector=off, **kw)
+                    torch.cuda.synchronize()
+                    ran_short += int(not all(torch.equal(a, b) for a, b in zip(gpu, again)))
+                    rep = compare_workload(wl, gpu, host=host, dense_order=order, name="small_workspace", **kw)
+                    assert not rep.failures, (order, listed, off, rep.failures[:3])
+    assert bool((buf[least:] == 0x5A).all())
+    assert ran_short > 0     # (other chunks, other rounding: the two plans did differ)

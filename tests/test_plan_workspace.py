@@ -1,10 +1,14 @@
 """The plan's short chunks never take a shape past a limit that the longest
 chunks keep: what fits the library's own scratch with four leading chunks and
-chunks of 9 blocks fits it, and what the work list holds with them is planned."""
+chunks of 9 blocks fits it, and what the work list holds with them is planned.
+One workspace serves every kind of walk over a shape, and the bytes that the
+longest chunks take are enough for any."""
+import os
+
 import pytest
 
 from paper_2606_00024_amd import _lib
-from test_abi_host import _opts, _shape, _ws
+from test_abi_host import _call, _call_static, _opts, _shape, _ws
 
 LIMIT = _lib.STATIC_SCRATCH_BYTES
 
@@ -62,3 +66,53 @@ def test_work_list_limit_kept(listed):
                    num_pages=1 << 20, max_pages_per_seq=1 if listed else t,
                    max_blocks_per_list=t if listed else 0)
     assert _ws(shape, _opts(dense_order=1))[1] == _lib.OK
+
+
+WALKS = [dict(dense_order=order, no_detector=off) for order in (0, 1) for off in (0, 1)]
+SHAPES = [(1, 8, 40, 64), (2, 64, 700, 128), (4, 64, 512, 64), (4, 2, 64, 64), (4, 500, 44, 64), (8, 256, 44, 64),
+          (8, 256, 900, 64), (16, 32, 300, 256), (4, 3000, 300, 64), (4, 60000, 40, 64), (1, 40000, 3400, 64)]
+
+
+def _shape_of(g, groups, t, block, listed=0):
+    return _shape(batch=groups, num_kv_heads=1, num_q_heads=g, block_size=block, page_size=64, num_pages=1 << 20,
+                  max_pages_per_seq=t * block // 64, max_blocks_per_list=listed)
+
+
+@pytest.mark.parametrize("per_head", [0, 1])
+@pytest.mark.parametrize("g,groups,t,block", SHAPES)
+def test_one_workspace_per_shape(g, groups, t, block, per_head):
+    sizes = {_ws(_shape_of(g, groups, t, block, listed), _opts(dense_order=order, per_head_stop=per_head))
+             for listed in (0, 1, t) for order in (0, 1)}
+    assert len(sizes) == 1 and sizes.pop()[1] == _lib.OK
+    # (without the test there are no per-head stops and no room for them)
+    sizes = {_ws(_shape_of(g, groups, t, block), _opts(**walk)) for walk in WALKS}
+    assert len(sizes) == 1
+
+
+@pytest.mark.parametrize("g,groups,t,block", SHAPES)
+def test_every_walk_runs_in_the_shape_s_workspace(g, groups, t, block):
+    """And in the bytes of the compact plan, but in no fewer."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("a GPU is visible: calls that pass the checks launch with placeholder pointers")
+    need = _ws(_shape_of(g, groups, t, block), _opts())[0]
+    least = _compact_chunks(g, groups, t, block)[1]
+    assert least <= need
+    for walk in WALKS:
+        for listed in (0, t):
+            shape, ptrs = _shape_of(g, groups, t, block, listed), dict(bl=16, bll=16) if listed else None
+            for size, status in ((need, _lib.ERR_HIP), (least, _lib.ERR_HIP), (least - 1, _lib.ERR_WORKSPACE_TOO_SMALL)):
+                assert _call(shape, _opts(**walk), ptrs, ws_bytes=size) == status, (walk, listed, size, need, least)
+            fits = need <= LIMIT
+            assert (_call_static(shape, _opts(**walk), ptrs) == _lib.ERR_WORKSPACE_TOO_SMALL) == (not fits)
+            assert fits == (least <= LIMIT)
+
+
+def test_workspace_of_longer_sequences():
+    """Sized for the longest sequences, and used for all shorter ones."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("a GPU is visible: calls that pass the checks launch with placeholder pointers")
+    for g, groups, most in ((4, 64, 512), (8, 256, 48), (4, 256, 1024)):
+        size = _ws(_shape_of(g, groups, most, 64), _opts())[0]
+        for t in range(1, most, max(1, most // 100)):
+            for walk in WALKS:
+                assert _call(_shape_of(g, groups, t, 64), _opts(**walk), ws_bytes=size) == _lib.ERR_HIP, (g, t, walk)
