@@ -69,8 +69,11 @@ __device__ __forceinline__ double wave_max(double x) {
 
 // A wavefront reads 64 tokens (one 16 KiB tile) of a block with coalesced
 // 16-byte loads: load i of lane l holds bytes 16*(l & 15) .. +15 of token
-// 4i + (l >> 4), which lies in 16-token piece i / 4 of the tile (a piece
-// never straddles a page: pages hold at least 16 tokens).
+// 4i + (l >> 4), which lies in 16-token piece i / 4 of the tile.  A piece
+// never straddles a page where pages hold at least 16 tokens and blocks begin
+// at multiples of 16 (WHOLE; every size that the decode call takes): one page
+// id per piece then serves its four loads.  For other sizes each load looks
+// up its own token's page.
 constexpr int kTileLoads = 16;
 constexpr int kRowPitch = 272;   // bytes per token row in the LDS tile (256 + 16 of padding)
 
@@ -164,20 +167,27 @@ __device__ __forceinline__ TilePos next_tile(const ListParams& P, const Walk& W,
     return first_tile(P, W, t.item + W.stride);
 }
 
-// Page of 16-token piece (lane & 3) of the tile, in lane n (n < 4).  Every
-// lane reads a valid entry; a tile past the end reads the first one.
-__device__ __forceinline__ int tile_pages(const ListParams& P, const TilePos& t, int64_t n_items,
-                                          int lane) {
-    const bool live = t.item < n_items;
-    const int tok = live ? min(t.t0 + 16 * (lane & 3), t.j1 - 1) : 0;
+// Page of a token of the tile's sequence.  Every lane reads a valid entry; a
+// tile past the end reads the first one.
+__device__ __forceinline__ int page_of(const ListParams& P, const TilePos& t, bool live, int tok) {
     const int64_t at = live ? (int64_t)t.b * P.max_pages + (tok >> P.page_shift) : 0;
     int pg = P.page_table[at];
     return pg < 0 ? 0 : (pg >= P.num_pages ? P.num_pages - 1 : pg);
 }
 
+// Page of 16-token piece (lane & 3) of the tile, in lane n (n < 4).
+template <bool WHOLE>
+__device__ __forceinline__ int tile_pages(const ListParams& P, const TilePos& t, int64_t n_items,
+                                          int lane) {
+    if constexpr (!WHOLE) return 0;
+    const bool live = t.item < n_items;
+    return page_of(P, t, live, live ? min(t.t0 + 16 * (lane & 3), t.j1 - 1) : 0);
+}
+
 // Rows past the tile's end read the tile's first row again, and every row
 // of a tile past the end of the work reads the pool's first row: the
 // callers ignore them, and they add no memory traffic beyond a line or two.
+template <bool WHOLE>
 __device__ __forceinline__ void load_tile(const ListParams& P, const TilePos& t, int pages, int64_t n_items,
                                           int lane, u32x4_l (&v)[kTileLoads]) {
     const int pmask = (1 << P.page_shift) - 1;
@@ -190,6 +200,7 @@ __device__ __forceinline__ void load_tile(const ListParams& P, const TilePos& t,
             tok = t.t0;
             pg = __builtin_amdgcn_readlane(pages, 0);
         }
+        if constexpr (!WHOLE) pg = page_of(P, t, live, tok);
         const uint16_t* row = live ? P.k + pg * P.ks_page + t.kvh * P.ks_head + (int64_t)(tok & pmask) * P.ks_tok
                                    : P.k;
         v[i] = reinterpret_cast<const u32x4_l*>(row)[lane & 15];
@@ -243,7 +254,7 @@ __device__ __forceinline__ Walk make_walk(const ListParams& P, WalkTable* table)
 // next tile's keys, so that waiting for them does not wait for the keys),
 // `tile_fn(t, v)` consumes a tile, `block_fn(t)` ends a block (after its
 // last tile).
-template <class PreFn, class TileFn, class BlockFn>
+template <bool WHOLE, class PreFn, class TileFn, class BlockFn>
 __device__ __forceinline__ void stream_tiles(const ListParams& P, const Walk& W, PreFn pre_fn,
                                              TileFn tile_fn, BlockFn block_fn) {
     const int lane = threadIdx.x & 63;
@@ -252,17 +263,17 @@ __device__ __forceinline__ void stream_tiles(const ListParams& P, const Walk& W,
     TilePos cur = first_tile(P, W, (int64_t)blockIdx.x * 4 + wave);
     if (cur.item >= n_items) return;
     TilePos nxt = next_tile(P, W, cur);
-    const int pg_cur = tile_pages(P, cur, n_items, lane);
-    int pg_nxt = tile_pages(P, nxt, n_items, lane);
+    const int pg_cur = tile_pages<WHOLE>(P, cur, n_items, lane);
+    int pg_nxt = tile_pages<WHOLE>(P, nxt, n_items, lane);
     u32x4_l a[kTileLoads], b[kTileLoads];
-    load_tile(P, cur, pg_cur, n_items, lane, a);
+    load_tile<WHOLE>(P, cur, pg_cur, n_items, lane, a);
     // One step: the page ids two tiles ahead, the keys of the next tile into
     // `nb`, then the current tile (in `cb`).  False once the work is done.
     auto step = [&](u32x4_l (&cb)[kTileLoads], u32x4_l (&nb)[kTileLoads]) -> bool {
         const TilePos nn = next_tile(P, W, nxt);
-        const int pg_nn = tile_pages(P, nn, n_items, lane);
+        const int pg_nn = tile_pages<WHOLE>(P, nn, n_items, lane);
         pre_fn(cur);
-        load_tile(P, nxt, pg_nxt, n_items, lane, nb);
+        load_tile<WHOLE>(P, nxt, pg_nxt, n_items, lane, nb);
         tile_fn(cur, cb);
         if (nxt.item != cur.item) block_fn(cur);
         if (nxt.item >= n_items) return false;
@@ -282,6 +293,7 @@ __device__ __forceinline__ void stream_tiles(const ListParams& P, const Walk& W,
 // again (load_tile), which leaves the maximum unchanged.
 constexpr int kKeyNormLds = 4 * 64 * kRowPitch;   // bytes per workgroup
 
+template <bool WHOLE>
 __global__ void __launch_bounds__(256) score_key_norm_kernel(const ListParams P) {
     extern __shared__ __align__(16) unsigned char tiles[];
     __shared__ WalkTable table;
@@ -289,7 +301,7 @@ __global__ void __launch_bounds__(256) score_key_norm_kernel(const ListParams P)
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     unsigned char* tile = tiles + w * 64 * kRowPitch;
     double best = -1.0;   // below any sum of squares
-    stream_tiles(P, W, [](const TilePos&) {},
+    stream_tiles<WHOLE>(P, W, [](const TilePos&) {},
         [&](const TilePos&, const u32x4_l (&v)[kTileLoads]) {
 #pragma unroll
             for (int i = 0; i < kTileLoads; ++i)
@@ -365,7 +377,7 @@ __device__ __forceinline__ void half_extremes(uint32_t smax, uint32_t smin, uint
     lo = __uint_as_float((ux >= 0x8000u ? ux : un) << 16);
 }
 
-template <int G>
+template <int G, bool WHOLE>
 __global__ void __launch_bounds__(256) score_query_bound_kernel(const ListParams P) {
     __shared__ double terms[4][G][128];
     __shared__ WalkTable table;
@@ -384,7 +396,7 @@ __global__ void __launch_bounds__(256) score_query_bound_kernel(const ListParams
     constexpr int QR = (G + 3) / 4;
     u32x4_l qw[QR];
     const int c = lane & 15, r = lane >> 4;
-    stream_tiles(P, W,
+    stream_tiles<WHOLE>(P, W,
         [&](const TilePos& t) {
 #pragma unroll
             for (int h0 = 0, u = 0; h0 < G; h0 += 4, ++u) {
@@ -784,6 +796,20 @@ __global__ void __launch_bounds__(kListThreads) select_kernel(const ListParams P
     if (tid == 0) P.list_len[gidx] = total_sel;
 }
 
+template <bool WHOLE>
+hipError_t launch_scores(const art_decode_shape* s, const art_list_opts* o, const ListParams& P, hipStream_t stream) {
+    const int64_t items = (int64_t)P.batch * P.num_kv_heads * P.max_blocks;
+    if (o->score_kind == ART_SCORE_KEY_NORM)
+        return launch_persistent(score_key_norm_kernel<WHOLE>, items, kKeyNormLds, stream, P, true);
+    switch (s->num_q_heads / s->num_kv_heads) {
+        case 1: return launch_persistent(score_query_bound_kernel<1, WHOLE>, items, 0, stream, P);
+        case 2: return launch_persistent(score_query_bound_kernel<2, WHOLE>, items, 0, stream, P);
+        case 4: return launch_persistent(score_query_bound_kernel<4, WHOLE>, items, 0, stream, P);
+        case 8: return launch_persistent(score_query_bound_kernel<8, WHOLE>, items, 0, stream, P);
+        default: return launch_persistent(score_query_bound_kernel<16, WHOLE>, items, 0, stream, P);
+    }
+}
+
 int ilog2_exact(int v) {
     int s = 0;
     while ((1 << s) < v) ++s;
@@ -884,21 +910,9 @@ art_status build_list(const art_decode_shape* shape, const art_list_opts* opts, 
     P.scores = scores;
     const int groups = shape->batch * shape->num_kv_heads;
     if (importance && (int64_t)groups * mb > 0) {
-        const int64_t waves = (int64_t)groups * mb;
-        if (opts->score_kind == ART_SCORE_KEY_NORM) {
-            if (launch_persistent(score_key_norm_kernel, waves, kKeyNormLds, stream, P, true) != hipSuccess)
-                return ART_ERR_HIP;
-        } else {
-            hipError_t e;
-            switch (shape->num_q_heads / shape->num_kv_heads) {
-                case 1: e = launch_persistent(score_query_bound_kernel<1>, waves, 0, stream, P); break;
-                case 2: e = launch_persistent(score_query_bound_kernel<2>, waves, 0, stream, P); break;
-                case 4: e = launch_persistent(score_query_bound_kernel<4>, waves, 0, stream, P); break;
-                case 8: e = launch_persistent(score_query_bound_kernel<8>, waves, 0, stream, P); break;
-                default: e = launch_persistent(score_query_bound_kernel<16>, waves, 0, stream, P); break;
-            }
-            if (e != hipSuccess) return ART_ERR_HIP;
-        }
+        const bool whole = shape->page_size >= 16 && shape->block_size % 16 == 0;
+        if ((whole ? launch_scores<true>(shape, opts, P, stream) : launch_scores<false>(shape, opts, P, stream)) != hipSuccess)
+            return ART_ERR_HIP;
     }
     const size_t lds = importance ? (size_t)sn * (sizeof(double) + sizeof(int)) +
                                         (kListThreads / 64 + 1) * sizeof(int)

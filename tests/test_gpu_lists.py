@@ -240,3 +240,16 @@ def test_selection_of_few_blocks(blocks):
         for budget, sinks, last in ((0, 0, False), (1, 0, True), (60, 4, True), (blocks // 3 - 1, 1, True),
                                     (blocks // 3, 0, False), (blocks // 3 + 1, 2, True), (3, blocks // 4, True)):
             _compare(wl, host, OL.IMPORTANCE, kind, budget, sinks, last)
+
+
+@pytest.mark.parametrize("block,page", [(64, 8), (24, 16), (40, 32), (100, 2), (8, 8), (200, 128), (72, 1), (48, 16)])
+def test_pieces_across_pages(block, page):
+    """Pages of fewer than 16 tokens, and blocks that do not begin at a
+    multiple of 16: 16 tokens from a block's start may lie in several pages
+    (in the last size they never do).  Lists take such sizes; decode calls
+    do not."""
+    host = small_workload(400 + block, batch=3, kv_heads=2, group=4, seq_len=(1333, 0, 700), block_size=block,
+                          page_size=page, needles=2)
+    wl = _to_dev(copy.copy(host))
+    for kind in (OL.KEY_NORM, OL.QUERY_BOUND):
+        _compare(wl, host, OL.IMPORTANCE, kind, 6, 1, True)
