@@ -104,9 +104,11 @@ Walk walk_of(const art_decode_shape* s, const art_decode_opts* o, bool listed) {
     return Walk{!o->no_detector, !o->no_detector && early};
 }
 
-// Everything about the launch is decided here from the shape, chunk_blocks
-// and the kind of walk: never from the data or the thresholds.  `compact`
-// keeps to the longest chunks and the fewest leading ones (see choose_plan).
+// Everything about the launch is decided here, never from the data.  What
+// the results' bits depend on comes from the shape, chunk_blocks and the kind
+// of walk alone; the thresholds have a say in the number of workgroups.
+// `compact` keeps to the longest chunks and the fewest leading ones (see
+// choose_plan).
 art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, Walk walk, bool compact, Plan* p) {
     const int g = s->num_q_heads / s->num_kv_heads;
     const int tpb = s->block_size / art::kTile;
@@ -174,10 +176,14 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, Walk
     // Workgroups per group, at most (never fewer than one per CU): beyond
     // that, a few long traversals gain nothing but reads past their stops.
     // Groups of up to 4 heads stop soonest: with 8 in place of 32, 32 such
-    // groups take 56 us in place of 75 on the 25 % lists and 39 in place of 52
-    // oldest-first, 87 in place of 92 recency-first at 4 x 32K tokens; if none
-    // of those stops, 125 in place of 118.
-    p->group_workgroups = !walk.detector || g > 4 ? 32 : 8;
+    // groups (g = 4) take 41 us in place of 67 on 25 % lists of 128K caches, 44
+    // in place of 63 oldest-first at 16K tokens, 83 in place of 92 recency-first
+    // at 32K.  Where none of them stops, 8 take 140 in place of 127, 72 in
+    // place of 67, 128 in place of 120: thresholds that no step can pass, and
+    // a patience that no traversal can reach, get 32.  (The number of workgroups
+    // changes no bit of the results.)
+    const bool stops = walk.detector && !o->no_detector && o->tau > 0.f && o->phi > 0.f && o->patience < t_cap;
+    p->group_workgroups = stops && g <= 4 ? 8 : 32;
     p->lead_chunks = lead_chunks;
     p->lead_blocks = lead_blocks;
     const int64_t max_chunks = chunks_for(t_cap, C, lead_chunks, lead_blocks);

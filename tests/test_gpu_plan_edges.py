@@ -110,3 +110,24 @@ def test_small_workspace(group):
                     assert not rep.failures, (order, listed, off, rep.failures[:3])
     assert bool((buf[least:] == 0x5A).all())
     assert ran_short > 0     # (other chunks, other rounding: the two plans did differ)
+
+
+@pytest.mark.parametrize("order", [0, 1])
+@pytest.mark.parametrize("group", [1, 4])
+def test_thresholds_that_never_pass(group, order):
+    """A launch whose thresholds cannot pass, or whose patience is out of
+    reach, may have more workgroups than one whose test just never fires: the
+    same bits from all of them."""
+    wl = small_workload(73, batch=5, kv_heads=4, group=group, seq_len=(5000, 4099, 64, 0, 3333),
+                        dense_order=order, device=DEV)
+    blocks = 79
+    lists = random_lists(wl, 9, fraction=0.8)
+    for listed in (False, True):
+        wl.block_list, wl.block_list_len = (x.to(DEV) for x in lists) if listed else (None, None)
+        fired = api.decode_workload(wl, tau=1e-30, phi=1e-30, patience=5)
+        for kw in (dict(tau=0.0, phi=1e-30, patience=5), dict(tau=1e-30, phi=-1.0, patience=5),
+                   dict(tau=0.5, phi=0.5, patience=blocks), dict(tau=0.5, phi=0.5, patience=2 ** 31 - 1)):
+            gpu = api.decode_workload(wl, **kw)
+            torch.cuda.synchronize()
+            for a, b in zip(fired, gpu):
+                assert torch.equal(a, b), (listed, kw)
