@@ -108,11 +108,6 @@ constexpr int kRowHalfMirror = 0x141; // lane i <- lane 7-i within each 8
 constexpr int kRowMirror = 0x140;     // lane i <- lane 15-i within each 16
 constexpr int kRowRor4 = 0x124;       // lane i <- lane i-4 of its row of 16 (= i+12)
 constexpr int kRowRor8 = 0x128;       // lane i <- lane i-8 (= i+8)
-constexpr int kRowRor12 = 0x12C;      // lane i <- lane i-12 (= i+4)
-template <int CTRL>
-__device__ __forceinline__ uint32_t dpp_u(uint32_t x) {
-  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, CTRL, 0xf, 0xf, false);
-}
 
 // Every lane of the row ends with the same bits (each step adds the same two
 // partial sums, only in swapped operand order).
@@ -197,31 +192,11 @@ __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sq
 __device__ __forceinline__ uint64_t ld_relaxed(const uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ __forceinline__ uint32_t ld_relaxed32(const uint32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 __device__ __forceinline__ int32_t ld_coh_i32(const int32_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 __device__ __forceinline__ void st_coh_i32(int32_t* p, int32_t v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ float ld_coh_f32(const float* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_coh_f32(float* p, float v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-// two adjacent floats through one 64-bit coherent access
-__device__ __forceinline__ void ld_coh_f32x2(const float* p, float& a, float& b) {
-  const uint64_t w = __hip_atomic_load(reinterpret_cast<const uint64_t*>(p), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-  a = __uint_as_float((uint32_t)w);
-  b = __uint_as_float((uint32_t)(w >> 32));
-}
-__device__ __forceinline__ void st_coh_f32x2(float* p, float a, float b) {
-  const uint64_t w = (uint64_t)__float_as_uint(a) | ((uint64_t)__float_as_uint(b) << 32);
-  __hip_atomic_store(reinterpret_cast<uint64_t*>(p), w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 // wait until this wave's global stores have completed; also a compiler
 // barrier for memory operations
@@ -317,11 +292,6 @@ __device__ __forceinline__ void state_clear(State<G>& s) {
 #pragma unroll
     for (int e = 0; e < 8; ++e) s.o[k][e] = 0.f;
   }
-}
-
-template <int G>
-__device__ __forceinline__ bool slot_valid(int lane, int k) {
-  return ((lane >> 4) + 4 * k) < G;
 }
 
 // s <- s (+) p_0 (+) p_1 ... : softmax-weighted merges of disjoint token
@@ -1244,10 +1214,6 @@ __device__ __forceinline__ int raw_list_len(Params& P, int gidx) {
   return P.block_list_len[P.list_per_head ? gidx : b];
 }
 
-__device__ __forceinline__ GroupInfo group_info(Params& P, int gidx) {
-  return group_info_raw(P, gidx, P.seq_lens[gidx / P.num_kv_heads], raw_list_len(P, gidx));
-}
-
 template <int G>
 __device__ void write_empty_wave(Params& P, int b, int kvh, int lane) {
   for (int i = lane; i < G * kD; i += 64) {
@@ -1431,7 +1397,6 @@ template <int G>
 __device__ void resolve_heads(Params& P, int gidx, int k, const GroupInfo& gi,
                               const float* blocks, const State<G>& pre, const Run<G>& run,
                               uint32_t head_bits, int t0, int nb, int lane) {
-  constexpr int REC = Cfg<G>::REC;
   const int n_chunks = gi.n_chunks, T = gi.T;
   const bool mine = lane < G;   // lane h holds head h
   int32_t* my = head_area(P, gidx, k, G) + lane * 8;
