@@ -97,8 +97,12 @@ struct Walk {
     bool early;     // and tends to stop the walk soon (see walk_of)
 };
 
-// Walks that tend to stop early: lists and oldest-first walks (the sinks
-// first) of groups of few heads.
+// Walks that tend to stop early: of groups of few heads, those over lists
+// (best blocks first, or the sinks and then the newest) and oldest-first ones
+// (the sinks first).  Groups of 8 and more heads stop later, if at all, and
+// lose as much as they gain: at g = 8 and thresholds of 1e-2, 25 % lists of 4 x 128K tokens
+// take 99 us with 16 leading chunks and 96 with 4, of 8 x 32K 70 and 74,
+// oldest-first 4 x 16K 70 and 67.
 Walk walk_of(const art_decode_shape* s, const art_decode_opts* o, bool listed) {
     const bool early = s->num_q_heads / s->num_kv_heads <= 4 && (listed || o->dense_order == ART_ORDER_FORWARD);
     return Walk{!o->no_detector, !o->no_detector && early};
@@ -145,13 +149,20 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, Walk
         // up to 9 blocks per chunk (12 without the test, which has nothing
         // to decide sooner), a multiple of the three loaders when the
         // budget allows; less when the whole problem has fewer than 64
-        // chunks, or when five chunks would cover the traversal (16 ragged
-        // sequences of up to 32 blocks, g = 4: 34.6 us with chunks of 9, 31.5
-        // with 6).  Without the test, 12 in place of 9 took 8 x 32K tokens
-        // from 212.8 to 205.0 us and 1 x 128K from 132 to 126.  (Halving the
-        // chunk whenever there were fewer chunks than 1024 cost 17-210 % on
-        // problems of 2 to 16 groups; the per-chunk work of the resolver
-        // outweighs the wider spread.)
+        // chunks, or when five chunks would cover the longest traversal that
+        // the shape allows (cache or list, whichever is longer).  The
+        // last rule serves short contexts, which are all latency: 16 ragged
+        // sequences of up to 2048 tokens, g = 4, 34.6 us with chunks of 9 and
+        // 31.5 with less, 16 x 1500 tokens 35.0 and 33.1 (g = 1), 37.2 and
+        // 34.2 (g = 4), 36.9 and 34.7 (g = 8), 48 x 2048 87.1 and 84.9 (g = 4);
+        // from 128 sequences on the records of more chunks take it back
+        // (256 x 2600: 267 and 270 at g = 1, 348 and 346 at g = 4, 564 and
+        // 573 at g = 8; without the test 485 and 512 at g = 4).
+        // Without the test, 12 in place of 9 took 8 x 32K tokens from 212.8 to
+        // 205.0 us and 1 x 128K from 132 to 126.  (Halving the chunk whenever
+        // there were fewer chunks than 1024 cost 17-210 % on problems of 2 to
+        // 16 groups; the per-chunk work of the resolver outweighs the wider
+        // spread.)
         const int most = walk.detector ? 9 : 12;
         C = c_max < most ? c_max : most;
         if (C >= 3) C -= C % 3;
@@ -164,9 +175,12 @@ art_status plan_chunks(const art_decode_shape* s, const art_decode_opts* o, Walk
     // Leading chunks of kLeadBlocks blocks: the first decisions of every
     // group come sooner, so that groups that stop early claim less past
     // their stop (only with the default chunk size).  Walks that tend to
-    // stop early have more of them: on 25 % lists of 128K caches 49.5 us with
-    // 16, 54 with 8, 56.5 with 4; oldest-first walks of 16K, 33 / 39 / 40; a
-    // recency-first batch of 8 x 32K, which stops later, 132 / 130 / 128.
+    // stop early have more of them: 25 % lists of 4 x 128K tokens take 41 us
+    // with 16, 46 with 8 and 46 with 4 at g = 4, 29 / 36 / 35 at g = 1, of
+    // 8 x 32K 52 / 66 / 64; oldest-first 4 x 16K 44 / 47 / 45, 8 x 32K 69 / 79
+    // / 77; a recency-first batch of 8 x 32K, which stops later, 132 / 130 /
+    // 128.  Where none of them stops the records of more chunks cost 5 us, of
+    // 122 on those lists of 4 x 128K and of 219 oldest-first at 8 x 32K.
     // Without the test there is nothing to decide.
     int lead_chunks = 0, lead_blocks = C;
     if (o->chunk_blocks == 0 && C > kLeadBlocks && walk.detector) {

@@ -88,7 +88,7 @@ struct KernelParams {
     int32_t lead_chunks, lead_blocks;  // the first lead_chunks chunks hold lead_blocks blocks
     int32_t work_chunks;     // chunk rows of the work list (<= max_chunks)
     int32_t v_in_record;     // 1: V is staged in the LDS record being written (no staging buffers)
-    int32_t wide;            // 1: rows of K or of V lie 8 MiB or more apart (64-bit lane addresses)
+    int32_t wide;            // 1: rows of K or of V lie 16 MiB or more apart (64-bit lane addresses)
     int32_t look_first;      // 1: a chunk looks back once before publishing its aggregate (set at launch)
     // data
     const uint16_t* q;

@@ -595,7 +595,7 @@ __device__ void compute_tile(Params& P, int kvh, int L, int tok0, const int (&pg
   // names.  V: lane (lo, g) holds token 4i + g, dims 8lo .. +7; the four
   // tokens of one load instruction are consecutive and lie in group i / 4.
   // All are issued together so that one memory latency covers the tile.
-  // Rows up to 8 MiB apart (WIDE false, every usual layout) are addressed
+  // Rows less than 16 MiB apart (WIDE false, every usual layout) are addressed
   // from scalar group bases with 24-bit lane products: the general form's
   // 64-bit multiplies per lane (36 of them) kept a tile's first loads waiting.
   u32x4 kr[4][4];

@@ -621,8 +621,12 @@ __device__ void merge_round(double* key, int* id, int total, int run) {
 // integers, 128 bins per octave, the last one open) gives a bin at or above
 // which at least `need` blocks lie; equal scores share a bin, and a higher
 // score never has a later one.  What bounds the selection is its sorting on one
-// CU, so it pays where a third of the blocks or fewer are wanted of more than
-// 1024: 512 of 2048 blocks 19.3 -> 16.5 us, 512 of 8192 73 -> 20.
+// CU, in steps of powers of two, so it pays where what is kept is sorted in a
+// smaller one: a third of the blocks or fewer, of more than 1024 (up to 1024
+// blocks are sorted in 9 us).  A quarter of 1088, 2048, 4096, 8192 blocks: 18.1
+// -> 12.7 us, 18.7 -> 15.2, 35.0 -> 23.6, 72 -> 46; a third 18.1 -> 12.5, 18.7
+// -> 15.3, 35.2 -> 24.8, 72 -> 43; a sixteenth of 8192 72 -> 20; but a half
+// 18.1 -> 14.5, 18.7 -> 22.8, 34.6 -> 39.0, 72 -> 79.
 constexpr int kFilterBlocks = 1024;
 constexpr int kFilterShift = 45;
 __device__ int keep_candidates(const double* sc, int n, int ns, bool last, int need, double* key, int* id,
