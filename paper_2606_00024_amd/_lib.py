@@ -118,7 +118,9 @@ def load_variant(path: str) -> ctypes.CDLL:
     lib.art_block_list_workspace_bytes.restype = ctypes.c_size_t
     lib.art_block_list_workspace_bytes.argtypes = [ctypes.POINTER(DecodeShape),
                                                    ctypes.POINTER(ListOpts), i32p]
-    for build in (lib.art_build_block_list, lib.art_build_block_list_padded):
+    for build in (lib.art_build_block_list, getattr(lib, "art_build_block_list_padded", None)):
+        if build is None:   # an earlier build of the same ABI version: every call but that one
+            continue
         build.restype = ctypes.c_int
         build.argtypes = [ctypes.POINTER(DecodeShape), ctypes.POINTER(ListOpts), vp, vp, vp, vp, vp,
                           vp, vp, vp, ctypes.c_size_t, vp]

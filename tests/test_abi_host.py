@@ -7,6 +7,7 @@ import ctypes
 import math
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -300,3 +301,16 @@ def test_work_list_must_fit_a_queue_word(lib):
     n, st = _ws(_shape(batch=64, num_kv_heads=8, num_q_heads=32, max_pages_per_seq=8192,
                        num_pages=1 << 20), _opts())
     assert st == _lib.OK and n > 0
+
+
+def test_earlier_builds_of_this_version_load(tmp_path):
+    """A build from before the padded list call has the same ABI version and
+    every other entry point: it loads for calls through those."""
+    names = [n for n in _lib.EXPORTS if n != "art_build_block_list_padded"]
+    src = tmp_path / "earlier.c"
+    src.write_text("\n".join(f"int {n}(void) {{ return {_lib.ABI_VERSION if n == 'art_abi_version' else 0}; }}"
+                             for n in names))
+    so = tmp_path / "libearlier.so"
+    subprocess.check_call(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)])
+    lib = _lib.load_variant(str(so))
+    assert int(lib.art_abi_version()) == _lib.ABI_VERSION and not hasattr(lib, "art_build_block_list_padded")
