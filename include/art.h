@@ -169,9 +169,9 @@ const char* art_status_str(int32_t status);
  * Workspace bytes that calls of this shape need: a function of the shape,
  * chunk_blocks and whether there are per-head stops, the same for every other
  * option, with and without a list.  Returns 0 and sets *status on invalid
- * input.  (A call also runs in as many bytes as its longest chunks take, which
- * is what a program has that sized its workspace for longer sequences than the
- * call's; then those are the chunks.)
+ * input.  (A call whose own split takes less runs in less; and one whose split
+ * takes more than it gets runs in longer chunks, if the workspace holds those:
+ * a program may have sized it for longer sequences than the call's.)
  */
 size_t art_decode_workspace_bytes(const art_decode_shape* shape,
                                   const art_decode_opts* opts, int32_t* status);
@@ -225,7 +225,8 @@ art_status art_decode_attention(const art_decode_shape* shape, const art_decode_
  *   - Arguments as for art_decode_attention, without the workspace.
  *   - A shape whose art_decode_workspace_bytes() exceeds
  *     ART_STATIC_SCRATCH_BYTES returns ART_ERR_WORKSPACE_TOO_SMALL before
- *     anything is launched.
+ *     anything is launched (but calls with no_detector, whose chunks are
+ *     longer, run as long as their own fit).
  *   - Every call on one GPU shares that GPU's array: calls that overlap on a
  *     GPU (different streams, or host threads issuing concurrently) race.
  *     Order them, for example on one stream.

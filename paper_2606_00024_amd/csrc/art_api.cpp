@@ -244,37 +244,41 @@ art_status choose_plan(const art_decode_shape* s, const art_decode_opts* o, Walk
     return st;
 }
 
-// Workspace bytes of a shape: `need`, the most that the plan of any kind of
-// walk takes, so that one workspace serves every order, lists or none, with
-// and without the test; and `least`, what the compact plan of a walk with the
-// test takes: a call that gets so much runs, if need be with that plan (a
-// program may size its workspace for its longest sequences, and the plan of
-// shorter ones can take more: 44 blocks in chunks of 6, 48 in chunks of 9).
-art_status workspace_of(const art_decode_shape* s, const art_decode_opts* o, size_t* need, size_t* least) {
+// Workspace bytes of a shape: the most that the plan of any kind of walk
+// takes, so that one workspace serves every order, lists or none, with and
+// without the test.  (A kind that no plan holds has no say, save the call's
+// own.)
+art_status workspace_of(const art_decode_shape* s, const art_decode_opts* o, size_t* need) {
     art_status st = check_shape(s, o);
     if (st != ART_OK) return st;
     Plan p;
-    st = plan_chunks(s, o, Walk{true, false}, true, &p);
+    st = choose_plan(s, o, walk_of(s, o, false), &p);
     if (st != ART_OK) return st;
-    *need = *least = p.ws.total;
-    for (const Walk walk : {Walk{true, false}, Walk{true, true}, Walk{false, false}}) {
-        st = choose_plan(s, o, walk, &p);
-        if (st != ART_OK) return st;
-        if (p.ws.total > *need) *need = p.ws.total;
-    }
+    *need = p.ws.total;
+    for (const Walk walk : {Walk{true, false}, Walk{true, true}, Walk{false, false}})
+        if (choose_plan(s, o, walk, &p) == ART_OK && p.ws.total > *need) *need = p.ws.total;
     return ART_OK;
 }
 
-// Host checks of a decode call, and its plan within `bytes` of workspace
-// (`scratch`: the library's own, for shapes whose workspace it holds).
+// A call's plan in `bytes` of workspace: where it takes more, the compact plan
+// of a walk with the test, which serves every kind.  (A program may size its
+// workspace for its longest sequences, and the plan of shorter ones can take
+// more: 44 blocks in chunks of 6, 48 in chunks of 9.)
+art_status fit_plan(const art_decode_shape* s, const art_decode_opts* o, size_t bytes, Plan* p) {
+    if (p->ws.total <= bytes) return ART_OK;
+    const art_status st = plan_chunks(s, o, Walk{true, false}, true, p);
+    return st == ART_OK && p->ws.total <= bytes ? ART_OK : ART_ERR_WORKSPACE_TOO_SMALL;
+}
+
+// Host checks of a decode call, and its plan within `bytes` of workspace.
 art_status check_decode_call(const art_decode_shape* shape, const art_decode_opts* opts,
                              const void* q, const void* k_cache, const void* v_cache,
                              const int32_t* page_table, const int32_t* seq_lens,
                              const int32_t* block_list, const int32_t* block_list_len,
                              const void* out, const float* lse, const int32_t* stop_block,
-                             size_t bytes, bool scratch, Plan* plan) {
-    size_t need = 0, least = 0;
-    art_status st = workspace_of(shape, opts, &need, &least);
+                             size_t bytes, Plan* plan) {
+    art_status st = check_shape(shape, opts);
+    if (st == ART_OK) st = choose_plan(shape, opts, walk_of(shape, opts, block_list != nullptr), plan);
     if (st != ART_OK) return st;
     if (shape->batch == 0) return ART_OK;
     if (!q || !k_cache || !v_cache || !page_table || !seq_lens || !out || !lse || !stop_block)
@@ -283,11 +287,7 @@ art_status check_decode_call(const art_decode_shape* shape, const art_decode_opt
     if (block_list && shape->max_blocks_per_list <= 0) return ART_ERR_INVALID_ARG;
     if (((uintptr_t)q | (uintptr_t)k_cache | (uintptr_t)v_cache | (uintptr_t)out) % 16)
         return ART_ERR_UNSUPPORTED;
-    if (bytes < (scratch ? need : least)) return ART_ERR_WORKSPACE_TOO_SMALL;
-    const Walk walk = walk_of(shape, opts, block_list != nullptr);
-    st = choose_plan(shape, opts, walk, plan);
-    if (st == ART_OK && plan->ws.total > bytes) st = plan_chunks(shape, opts, Walk{true, false}, true, plan);
-    return st;
+    return fit_plan(shape, opts, bytes, plan);
 }
 
 // Kernel parameters of a checked call over the workspace at `workspace`,
@@ -389,8 +389,8 @@ const char* art_status_str(int32_t status) {
 
 size_t art_decode_workspace_bytes(const art_decode_shape* shape, const art_decode_opts* opts,
                                   int32_t* status) {
-    size_t need = 0, least = 0;
-    const art_status st = workspace_of(shape, opts, &need, &least);
+    size_t need = 0;
+    const art_status st = workspace_of(shape, opts, &need);
     if (status) *status = st;
     return st == ART_OK ? need : 0;
 }
@@ -411,7 +411,7 @@ art_status art_decode_attention(const art_decode_shape* shape, const art_decode_
     Plan plan;
     art_status st = check_decode_call(shape, opts, q, k_cache, v_cache, page_table, seq_lens,
                                       block_list, block_list_len, out, lse, stop_block,
-                                      workspace ? workspace_bytes : 0, false, &plan);
+                                      workspace ? workspace_bytes : 0, &plan);
     if (st != ART_OK || shape->batch == 0) return st;
     if ((uintptr_t)workspace % 8) return ART_ERR_INVALID_ARG;
     return enqueue_decode(plan, shape, opts, q, k_cache, v_cache, page_table, seq_lens,
@@ -427,7 +427,7 @@ art_status art_decode_attention_static(const art_decode_shape* shape, const art_
     Plan plan;
     art_status st = check_decode_call(shape, opts, q, k_cache, v_cache, page_table, seq_lens,
                                       block_list, block_list_len, out, lse, stop_block,
-                                      ART_STATIC_SCRATCH_BYTES, true, &plan);
+                                      ART_STATIC_SCRATCH_BYTES, &plan);
     if (st != ART_OK || shape->batch == 0) return st;
     void* scratch = nullptr;
     if (art::static_scratch(stream, &scratch) != (int)hipSuccess) return ART_ERR_HIP;

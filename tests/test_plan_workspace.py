@@ -91,7 +91,7 @@ def test_one_workspace_per_shape(g, groups, t, block, per_head):
 
 @pytest.mark.parametrize("g,groups,t,block", SHAPES)
 def test_every_walk_runs_in_the_shape_s_workspace(g, groups, t, block):
-    """And in the bytes of the compact plan, but in no fewer."""
+    """And in the bytes of the compact plan; under the test, in no fewer."""
     if os.path.exists("/dev/kfd"):
         pytest.skip("a GPU is visible: calls that pass the checks launch with placeholder pointers")
     need = _ws(_shape_of(g, groups, t, block), _opts())[0]
@@ -100,11 +100,33 @@ def test_every_walk_runs_in_the_shape_s_workspace(g, groups, t, block):
     for walk in WALKS:
         for listed in (0, t):
             shape, ptrs = _shape_of(g, groups, t, block, listed), dict(bl=16, bll=16) if listed else None
-            for size, status in ((need, _lib.ERR_HIP), (least, _lib.ERR_HIP), (least - 1, _lib.ERR_WORKSPACE_TOO_SMALL)):
-                assert _call(shape, _opts(**walk), ptrs, ws_bytes=size) == status, (walk, listed, size, need, least)
-            fits = need <= LIMIT
-            assert (_call_static(shape, _opts(**walk), ptrs) == _lib.ERR_WORKSPACE_TOO_SMALL) == (not fits)
-            assert fits == (least <= LIMIT)
+            for size in (need, least):
+                assert _call(shape, _opts(**walk), ptrs, ws_bytes=size) == _lib.ERR_HIP, (walk, listed, size, need, least)
+            static = _call_static(shape, _opts(**walk), ptrs)
+            if need <= LIMIT:
+                assert static == _lib.ERR_HIP
+            if not walk["no_detector"]:
+                assert _call(shape, _opts(**walk), ptrs, ws_bytes=least - 1) == _lib.ERR_WORKSPACE_TOO_SMALL
+                assert static == (_lib.ERR_HIP if least <= LIMIT else _lib.ERR_WORKSPACE_TOO_SMALL)
+    assert (need <= LIMIT) == (least <= LIMIT)
+
+
+def test_full_attention_runs_in_its_own_bytes():
+    """Without the test the chunks are longer and there are no leading ones:
+    such calls take less than the shape's workspace, the static scratch too."""
+    if os.path.exists("/dev/kfd"):
+        pytest.skip("a GPU is visible: calls that pass the checks launch with placeholder pointers")
+    g, groups, t = 4, 64, 2200
+    shape, record = _shape_of(g, groups, t, 64), (g * 128 + 2 * g + 63) // 64 * 64
+    chunks = -(-t // 12)
+    up = lambda x: (x + 255) // 256 * 256
+    own = up(8) + up(8 * 32 * 8) + up(8 * groups) + up(8 * groups * chunks) + up(groups * chunks * 2 * record * 4)
+    assert own <= LIMIT < _compact_chunks(g, groups, t, 64)[1]
+    off = _opts(no_detector=1)
+    assert _call(shape, off, ws_bytes=own) == _lib.ERR_HIP
+    assert _call(shape, off, ws_bytes=own - 1) == _lib.ERR_WORKSPACE_TOO_SMALL
+    assert _call_static(shape, off) == _lib.ERR_HIP
+    assert _call_static(shape, _opts()) == _lib.ERR_WORKSPACE_TOO_SMALL
 
 
 def test_workspace_of_longer_sequences():
